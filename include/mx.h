@@ -112,10 +112,14 @@ typedef struct mx_config {
                              LDS tile: <= 8.
                              3D: up to 3 in FP32, 2 in FP64 (library choice: the
                              most allowed). */
-    int variant;          /* 2D sweep kernel: 0 library choice (FP32: 4, FP64 and
-                             the Chebyshev solve: 3; Alg 1 on a grid whose
-                             streaming pass would have fewer workgroups than
-                             half the CUs: 1),
+    int variant;          /* 2D sweep kernel: 0 library choice (fixed counts of
+                             Alg 1 with sweeps_per_pass = 0 on grids of up to
+                             3.4 million cells in FP32 with both blocks, 4.3
+                             million else: register tiles, which cut the count
+                             into passes by a time model of their own; else
+                             FP32: 4, FP64 and the Chebyshev solve: 3; Alg 1 on
+                             a grid whose streaming pass would have fewer
+                             workgroups than half the CUs: 1),
                              1 LDS tile (both blocks per pass; by default 5
                              sweeps deep in FP32, 4 in FP64, 8 under a
                              tolerance), 2 row streaming
@@ -191,8 +195,9 @@ int mx_step(mx_grid *g, int nsteps, const double *env, const int *replay, mx_ste
 int mx_get_step(mx_grid *g, int64_t *n);
 int mx_set_step(mx_grid *g, int64_t n);
 
-/* Sweeps fused per HBM pass in use (the library's or the configured choice):
-   that of the TE block when it is active, else that of TM.  With a fixed m
+/* Sweeps fused per HBM pass in use (the library's or the configured choice;
+   of the row-streaming or LDS-tile kernel, not of register tiles): that of
+   the TE block when it is active, else that of TM.  With a fixed m
    a block's m sweeps run in the fewest passes of at most this depth, of
    nearly equal depth, the deeper ones last; under a tolerance the stop
    test follows every pass, and both 2D blocks then use one depth unless

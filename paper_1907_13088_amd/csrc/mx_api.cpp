@@ -163,6 +163,9 @@ struct mx_grid {
     int variant;          // 2D sweep kernel in use: 1 LDS tile, 2 row streaming (blocks
                           // together), 3 row streaming (each block on its own), 4 as 2
                           // with the front fused into the first pass where possible
+    bool reg = false;     // 2D, library choice: fixed counts of Alg 1 run on register tiles
+    RegPlan plan[2][3];   // their plans ([front][block set - 1]) for the counts plan_m
+    int plan_m[2][3] = {{-1, -1, -1}, {-1, -1, -1}};
     Coef<float> cf;
     Coef<double> cd;
     // Chebyshev solve: per block, the factors (previous increment, residual)
@@ -316,6 +319,9 @@ static void grid_setup(mx_grid *g, const mx_config *cfg, hipStream_t stream, int
         if (stream_workgroups(cfg, g->variant, cu) < cu / 2) g->variant = 1;
     }
     pass_depths(cfg, g->variant, g->spp);
+    // fixed counts on grids of up to a few million cells: register tiles
+    g->reg = cfg->ndim == 2 && cfg->variant == 0 && cfg->sweeps_per_pass == 0 && cfg->solver == MX_SOLVER_ALG1 &&
+             reg_pays(cfg->dtype == MX_F64, cfg->blocks, cfg->n[0], cfg->n[1]);
     const size_t arr = up((size_t)g->ncell * elem_of(cfg));
     char *p = g->ws;
     auto take = [&](void **dst) { *dst = p; p += arr; };
@@ -762,12 +768,134 @@ struct FusedFront {
     const T *Bin[3];
 };
 
+// The register-tile plan of one solve of m sweeps (kept per grid: a run
+// repeats its count)
+const RegPlan &reg_plan_of(mx_grid *g, int blocks, bool front, int m)
+{
+    RegPlan &p = g->plan[front][blocks - 1];
+    if (g->plan_m[front][blocks - 1] != m) {
+        p = reg_plan(g->cfg.dtype == MX_F64, blocks, front, g->cfg.n[0], g->cfg.n[1], m);
+        g->plan_m[front][blocks - 1] = m;
+    }
+    return p;
+}
+
+// One solve on register tiles: with `front` (its E, B, Jf, env_src set) the
+// whole step including E += x, else x = sum_{j<count} A^j rhs left in
+// res[3].  Both blocks run in one set of passes when their counts agree and
+// that is modelled faster (FP64 tiles of both blocks hold few cells in
+// registers).
+template <typename T>
+int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int target[2], const T **res)
+{
+    const mx_config &c = g->cfg;
+    const Coef<T> &k = coef<T>(g);
+    int groups[2] = {c.blocks & 1, c.blocks & 2};
+    if (c.blocks == MX_ALL && target[0] == target[1] &&
+        reg_plan_of(g, 3, front != nullptr, target[0]).us <=
+            reg_plan_of(g, 1, front != nullptr, target[0]).us + reg_plan_of(g, 2, front != nullptr, target[1]).us) {
+        groups[0] = 3;
+        groups[1] = 0;
+    }
+    for (int q = 0; q < 3 && !front; q++) res[q] = (const T *)rhs[q];
+    for (int gi = 0; gi < 2; gi++) {
+        const int blk = groups[gi];
+        if (!blk) continue;
+        const int m = target[blk == 2 ? 1 : 0];
+        if (m == 0 && !front) continue;
+        const RegPlan &p = reg_plan_of(g, blk, front != nullptr, m);
+        const int ncomp = blk == 3 ? 3 : (blk == 1 ? 2 : 1);
+        const double arr = (double)g->ncell * sizeof(T);
+        for (int i = 0, rem = m; i < p.passes; i++) {
+            const int kind = front && i == 0 ? RK_FRONT : (front && i == p.passes - 1 ? RK_LAST : RK_MID);
+            RegArgs<T> a = front ? *front : RegArgs<T>{};
+            a.k = rem / (p.passes - i);
+            const int cb = (i - 1) & 1, ob = i & 1;
+            for (int q = 0; q < 3; q++) {
+                a.dEp[q] = (T *)rhs[q];
+                a.rhs[q] = (const T *)rhs[q];
+                a.x_in[q] = i == 0 ? (const T *)rhs[q] : (const T *)g->X[cb][q];
+                a.x_out[q] = (T *)g->X[ob][q];
+            }
+            hipError_t e;
+            {
+                // front: E, B, J read, B, dE', x written; others as the streaming passes
+                const int nb = blk == 3 ? 3 : (blk == 1 ? 1 : 2);
+                const int arrays = kind == RK_FRONT ? ncomp * (front->Jf[0] ? 4 : 3) + 2 * nb
+                                                    : ncomp * pass_arrays(false, false, !front && i == 0, kind == RK_LAST);
+                ProfScope ps(g, kind == RK_FRONT ? MX_PROF_FRONT_SWEEP : kind == RK_LAST ? MX_PROF_SWEEP_LAST : MX_PROF_SWEEP,
+                             arr * arrays);
+                e = launch_reg<T>(k, blk, p.geo, kind, a, g->stream);
+            }
+            if (e != hipSuccess) return fail(MX_EDEVICE, "register-tile pass: %s", hipGetErrorString(e));
+            rem -= a.k;
+            if (!front)
+                for (int q = 0; q < 3; q++)
+                    if (blk & (q == 2 ? 2 : 1)) res[q] = (const T *)g->X[ob][q];
+        }
+    }
+    return MX_OK;
+}
+
+// nsteps steps of fixed counts of Alg 1 on register tiles
+template <typename T>
+int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_step_stats *stats)
+{
+    const mx_config &c = g->cfg;
+    // the current's filter is the same at every step of the call: applied once
+    // (S is free: fixed counts keep no running sum)
+    void *const *Jf = g->J0;
+    if (g->has_j && c.filter_passes > 0 && nsteps > 0) {
+        const int mask = ((c.blocks & 1) ? 3 : 0) | ((c.blocks & 2) ? 4 : 0);
+        ProfScope ps(g, MX_PROF_FRONT, (double)g->ncell * sizeof(T) * 2 * __builtin_popcount(mask));
+        HIPCHK(launch_filter2d<T>(coef<T>(g), c.filter_passes, mask, (const T *const *)g->J0, (T *const *)g->S, g->stream));
+        Jf = g->S;
+    }
+    for (int s = 0; s < nsteps; s++) {
+        int target[2];
+        for (int b = 0; b < 2; b++) {
+            target[b] = replay ? replay[2 * s + b] : (c.lumped ? 0 : c.sweeps);
+            if (target[b] < 0) return fail(MX_EINVAL, "negative replayed sweep count at step %d", s);
+            if (!(c.blocks & (1 << b))) target[b] = 0;
+        }
+        RegArgs<T> a{};
+        a.env_src = (T)((env ? env[s] : 0.0) * c.four_pi * c.dt);
+        for (int q = 0; q < 3; q++) {
+            const bool act = q == 2 ? (c.blocks & 1) : (c.blocks & 2);
+            a.E[q] = (T *)g->E[q];
+            a.Jf[q] = g->has_j ? (const T *)Jf[q] : nullptr;
+            a.Bin[q] = (const T *)(g->bloc[q] ? g->Bws[q] : g->B[q]);
+            a.B[q] = (T *)(g->bloc[q] ? g->B[q] : g->Bws[q]);
+            if (act) g->bloc[q] ^= 1;
+            // the call's last step hands B back in its last pass
+            if (act && s == nsteps - 1 && g->bloc[q]) {
+                a.Bs[q] = (const T *)g->Bws[q];
+                a.Bd[q] = (T *)g->B[q];
+                g->bloc[q] = 0;
+            }
+        }
+        const int rc = reg_solve<T>(g, &a, g->dEp, target, nullptr);
+        if (rc) return rc;
+        if (stats) {
+            stats[s] = mx_step_stats{};
+            for (int b = 0; b < 2; b++) stats[s].sweeps[b] = target[b];
+        }
+        g->step++;
+    }
+    return MX_OK;
+}
+
 template <typename T>
 int run_sweeps(mx_grid *g, void *const rhs[3], const int *target_in, bool tolmode, void *E_fuse[3],
                bool e_done[2], const T **res, mx_step_stats *st, const FusedFront<T> *ff = nullptr)
 {
     e_done[0] = e_done[1] = false;
     if (tolmode) return solve_tol<T>(g, rhs, target_in, res, st);
+    if (g->reg && !E_fuse) {
+        int t[2];
+        for (int b = 0; b < 2; b++) t[b] = (g->cfg.blocks & (1 << b)) ? target_in[b] : 0;
+        return reg_solve<T>(g, nullptr, rhs, t, res);   // the transposed step's solve (no record asked for)
+    }
     const mx_config &c = g->cfg;
     const Coef<T> &k = coef<T>(g);
     const int nblk = c.ndim == 3 ? 1 : 2;
@@ -947,6 +1075,10 @@ int step_impl(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
         const int rc = small_steps<T>(g, nsteps, env, stats);
         if (rc) return rc;
         nsteps = 0;   // done; the hand-back below returns B to the caller's buffers
+    } else if (g->reg && !tolmode) {
+        const int rc = reg_steps<T>(g, nsteps, env, replay, stats);
+        if (rc) return rc;
+        nsteps = 0;
     }
     for (int s = 0; s < nsteps; s++) {
         const double e = env ? env[s] : 0.0;

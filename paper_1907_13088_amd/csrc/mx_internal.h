@@ -232,6 +232,39 @@ bool front_sweep2d_ok(bool f64, int k, int filter_passes);
 template <typename T>
 hipError_t launch_front_sweep2d(const Coef<T> &c, int filter_passes, int k, const FrontArgs<T> &fa,
                                 const T *const Bin[3], const SweepArgs<T> &sa, hipStream_t s, int *nwg);
+// Register-tile passes for grids too small for row streams (k2r_impl.h)
+enum : int { RK_FRONT = 0, RK_MID = 1, RK_LAST = 2 };   // kinds of pass
+template <typename T>
+struct RegArgs {
+    T *E[3];              // front: E^n, read; last pass: E += x
+    const T *Bin[3];      // front: B^{n-1/2}
+    T *B[3];              // front: B^{n+1/2} out
+    const T *Jf[3];       // front: the filtered current (null: none)
+    T env_src;
+    T *dEp[3];            // front: dE' out
+    const T *rhs[3];      // other passes: dE'
+    const T *x_in[3];     // other passes: the iterate (rhs on the first pass)
+    T *x_out[3];          // passes that store the iterate
+    const T *Bs[3];       // last pass: B handed back, Bd = Bs on the own cells (null: none)
+    T *Bd[3];
+    int k;                // sweeps
+};
+// How one solve of m sweeps of a block set is cut: the tile geometry and the
+// number of passes (front + others when `front`, else passes without one);
+// geo < 0: no plan
+struct RegPlan {
+    int geo, passes;
+    double us;            // modelled time
+};
+RegPlan reg_plan(bool f64, int blocks, bool front, int64_t nx, int64_t ny, int m);
+// grids that the register tiles step faster than the row streams do
+bool reg_pays(bool f64, int blocks, int64_t nx, int64_t ny);
+template <typename T>
+hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, const RegArgs<T> &a, hipStream_t s);
+// out = p binomial passes per axis of the components of mask (2D)
+template <typename T>
+hipError_t launch_filter2d(const Coef<T> &c, int passes, int mask, const T *const J0[3], T *const out[3], hipStream_t s);
+
 template <typename T>
 hipError_t launch_update(int64_t n, int comp_mask, T *const E[3], const T *const X[3], hipStream_t s);
 
