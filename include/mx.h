@@ -306,7 +306,7 @@ int mx_adjoint(mx_grid *g, int nsteps, const double *env, const int *sweeps,
  * than a cell per step: |v| < 1 and dt obeys the CFL bound.  The
  * deposition adds with floating-point atomics: J is reproducible up to the
  * order of those additions (rounding).  Needs blocks = MX_ALL; the bound
- * fields are read, not changed.
+ * fields are read, not changed; the grid's workspace is used.
  *
  * mx_pic_charge: rho at the nodes (i, j) (device, grid dtype) of the same
  * particles, the density whose change the deposition's current carries;

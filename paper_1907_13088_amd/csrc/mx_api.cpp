@@ -1401,7 +1401,8 @@ int pic_push_impl(mx_grid *g, int64_t np, double q, double m, double w, void *co
     a.Lx = (T)(c.n[0] * c.d[0]);
     a.Ly = (T)(c.n[1] * c.d[1]);
     ProfScope ps(g, MX_PROF_PARTICLES, (double)np * sizeof(T) * 10);
-    HIPCHK(launch_pic_push<T>(a, zero_j, g->stream));
+    // the iterate buffers (six arrays, consecutive) are free between steps
+    HIPCHK(launch_pic_push<T>(a, zero_j, g->X[0][0], g->stream));
     return MX_OK;
 }
 

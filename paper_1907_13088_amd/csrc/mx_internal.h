@@ -329,8 +329,9 @@ struct PicArgs {
     T cx, cy, cz;         // -q w / (dy dt), -q w / (dx dt), q w / (dx dy)
     T Lx, Ly;             // nx dx, ny dy
 };
+// scratch: five values per cell
 template <typename T>
-hipError_t launch_pic_push(const PicArgs<T> &a, bool zero_j, hipStream_t s);
+hipError_t launch_pic_push(const PicArgs<T> &a, bool zero_j, void *scratch, hipStream_t s);
 template <typename T>
 hipError_t launch_pic_charge(int64_t np, int nx, int ny, T dx, T dy, T cq, const T *x, const T *y, T *rho,
                              bool zero_rho, hipStream_t s);
