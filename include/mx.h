@@ -112,12 +112,12 @@ typedef struct mx_config {
                              LDS tile: <= 8.
                              3D: up to 3 in FP32, 2 in FP64 (library choice: the
                              most allowed). */
-    int variant;          /* 2D sweep kernel: 0 library choice (fixed counts of
-                             Alg 1 with sweeps_per_pass = 0 on grids of up to
-                             3.4 million cells in FP32 with both blocks, 4.3
-                             million else: register tiles, which cut the count
-                             into passes by a time model of their own; else
-                             FP32: 4, FP64 and the Chebyshev solve: 3; Alg 1 on
+    int variant;          /* 2D sweep kernel: 0 library choice (with
+                             sweeps_per_pass = 0, on grids of up to 1.3 to 5.5
+                             million cells by dtype, blocks and solve: register
+                             tiles, which cut a fixed count into passes by a
+                             time model of their own and a tolerance solve at
+                             the depths below; else FP32: 4, FP64 and the Chebyshev solve: 3; Alg 1 on
                              a grid whose streaming pass would have fewer
                              workgroups than half the CUs: 1),
                              1 LDS tile (both blocks per pass; by default 5
@@ -184,8 +184,8 @@ int mx_set_current(mx_grid *g, void *const J0[3]);
    unless tol > 0: then the stop test runs on the device after every pass,
    passes are queued ahead of it (as many per block as the previous step
    needed; those after convergence do nothing) and the call waits about
-   once per step to read the outcome; a non-finite norm is reported at
-   that read. */
+   once per step, on register tiles once per up to 64 steps, to read the
+   outcome; a non-finite norm is reported at that read. */
 int mx_step(mx_grid *g, int nsteps, const double *env, const int *replay, mx_step_stats *stats);
 /* (With the environment variable MX_STATS set, mx_step also writes each
    step's record as one JSON line: MX_STATS=1 to stderr, any other value
@@ -196,8 +196,8 @@ int mx_get_step(mx_grid *g, int64_t *n);
 int mx_set_step(mx_grid *g, int64_t n);
 
 /* Sweeps fused per HBM pass in use (the library's or the configured choice;
-   of the row-streaming or LDS-tile kernel, not of register tiles): that of
-   the TE block when it is active, else that of TM.  With a fixed m
+   of the row-streaming or LDS-tile kernel, and of tolerance solves on register
+   tiles, not of their fixed counts): that of the TE block when it is active, else that of TM.  With a fixed m
    a block's m sweeps run in the fewest passes of at most this depth, of
    nearly equal depth, the deeper ones last; under a tolerance the stop
    test follows every pass, and both 2D blocks then use one depth unless

@@ -4,71 +4,104 @@
 #include <algorithm>
 #include <cmath>
 
-#include "k2f_impl.h"
-#include "mx_internal.h"
+#include "k2r_impl.h"
 
 namespace mx {
 namespace reg2d {
 
-template <typename T, int BLK>
-hipError_t launch(const Coef<T> &c, int geo, int kind, const RegArgs<T> &a, hipStream_t s);
-#define MX_REG_EXTERN(T)                                                                             \
-    extern template hipError_t launch<T, 1>(const Coef<T> &, int, int, const RegArgs<T> &, hipStream_t); \
-    extern template hipError_t launch<T, 2>(const Coef<T> &, int, int, const RegArgs<T> &, hipStream_t); \
-    extern template hipError_t launch<T, 3>(const Coef<T> &, int, int, const RegArgs<T> &, hipStream_t);
-MX_REG_EXTERN(float)
-MX_REG_EXTERN(double)
+template <typename T, int FORM, bool TOL>
+hipError_t launch(const Coef<T> &c, int mask, int geo, int kind, const RegArgs<T> &a, hipStream_t s, int *npart);
+#define MX_REG_EXTERN(T, F, TOL) \
+    extern template hipError_t launch<T, F, TOL>(const Coef<T> &, int, int, int, const RegArgs<T> &, hipStream_t, int *);
+#define MX_REG_EXTERN_T(T)                                                                                             \
+    MX_REG_EXTERN(T, FM_STD, false) MX_REG_EXTERN(T, FM_CHEB, false) MX_REG_EXTERN(T, FM_STD, true)                     \
+    MX_REG_EXTERN(T, FM_DELTA, true) MX_REG_EXTERN(T, FM_CHEB, true)
+MX_REG_EXTERN_T(float)
+MX_REG_EXTERN_T(double)
+#undef MX_REG_EXTERN_T
 #undef MX_REG_EXTERN
 
 // Tile geometries: columns and rows of the region.  Two neighbouring columns
-// per lane halve the lane shifts and widen the region, at registers that
-// leave both blocks together no room.
+// per lane (FP32) halve the lane shifts and widen the region; in FP64 they
+// leave a CU one workgroup, and nothing hides its loads (1500 x 1100, 8
+// sweeps, TE 72 against 41 us).
 struct Geo {
     int rx, ry;
 };
 constexpr Geo GEO[4] = {{64, 32}, {64, 32}, {64, 64}, {128, 64}};
 
 // Time of a pass (us) with c workgroups per CU: t0 + c load[kind] + k (c s + s0),
-// fitted to sweeps over grids from 128^2 to 4096 x 2048, depths 0 to 14 and
-// every geometry (relative rms 6 to 14 %; the choice it makes is within 6 %
-// of the best measured one on most grids).  Rows: FP32 TE, TM, both, FP64
-// the same; columns: geometry.
+// fitted to sweeps over grids from 128^2 to 2048^2, depths 0 to 14, every
+// geometry, each block alone and both in one launch (relative rms 5 to 20 %;
+// the choice it makes is within 3 % of the best measured one on average, 35 %
+// at worst).  By form (standard and delta, Chebyshev), type and blocks,
+// geometry.
 struct Fit {
     double t0, load[3], s, s0;
 };
-constexpr Fit FIT[6][4] = {
-        {{1.31, {1.92, 1.50, 1.97}, 0.083, 0.214},
-         {1.70, {1.79, 1.23, 1.76}, 0.022, 0.271},
-         {0.00, {4.01, 3.12, 4.14}, 0.123, 0.368},
-         {1.24, {9.16, 6.75, 8.65}, 0.094, 0.629}},   // F32 TE
-        {{1.58, {1.62, 1.00, 1.14}, 0.113, 0.151},
-         {1.88, {1.41, 0.70, 0.87}, 0.061, 0.181},
-         {1.01, {3.06, 1.71, 2.08}, 0.176, 0.224},
-         {1.58, {7.83, 3.42, 4.21}, 0.176, 0.400}},   // F32 TM
-        {{0.62, {3.70, 2.40, 3.27}, 0.113, 0.357},
-         {0.87, {3.47, 2.24, 3.21}, 0.028, 0.491},
-         {0.00, {6.41, 3.90, 5.63}, 0.376, 0.392}},   // F32 both
-        {{0.74, {3.81, 3.12, 3.81}, 0.023, 0.382},
-         {1.24, {3.45, 2.68, 3.44}, 0.000, 0.396},
-         {0.00, {7.15, 5.60, 6.84}, 0.182, 0.440},
-         {0.00, {13.36, 9.45, 11.88}, 1.001, 0.000}},   // F64 TE
-        {{1.27, {2.93, 1.49, 1.80}, 0.135, 0.251},
-         {1.55, {2.74, 1.24, 1.56}, 0.065, 0.313},
-         {0.28, {6.87, 2.92, 3.47}, 0.265, 0.281},
-         {0.00, {11.83, 5.62, 6.54}, 0.853, 0.000}},   // F64 TM
-        {{0.00, {8.61, 4.50, 5.54}, 0.179, 0.416},
-         {0.00, {7.16, 4.74, 6.54}, 0.053, 0.462},
-         {0.00, {12.09, 7.46, 9.70}, 1.114, 0.000}},   // F64 both
-};
+constexpr Fit FIT[2][6][4] = {
+    {
+     {{2.65, {1.72, 1.37, 1.75}, 0.131, 0.069},
+      {3.18, {1.46, 0.98, 1.58}, 0.066, 0.145},
+      {1.39, {3.50, 2.72, 3.93}, 0.166, 0.270},
+      {1.23, {9.68, 6.70, 9.25}, 0.084, 0.695}},   // FP32 TE
+     {{3.07, {1.45, 0.77, 1.00}, 0.146, 0.028},
+      {3.45, {1.18, 0.51, 0.75}, 0.090, 0.056},
+      {2.68, {2.54, 1.30, 1.90}, 0.222, 0.092},
+      {2.05, {8.25, 3.23, 4.53}, 0.177, 0.414}},   // FP32 TM
+     {{2.28, {1.79, 1.40, 1.89}, 0.107, 0.122},
+      {2.69, {1.65, 1.12, 1.71}, 0.041, 0.198},
+      {1.39, {3.68, 2.73, 3.97}, 0.148, 0.273},
+      {1.34, {9.42, 6.70, 8.93}, 0.104, 0.655}},   // FP32 both
+     {{2.21, {3.56, 2.77, 3.42}, 0.127, 0.173},
+      {2.44, {3.28, 2.51, 3.35}, 0.027, 0.302},
+      {0.02, {7.36, 5.97, 7.52}, 0.144, 0.467}},   // FP64 TE
+     {{3.36, {2.52, 1.23, 1.51}, 0.189, 0.081},
+      {3.52, {2.66, 1.04, 1.34}, 0.105, 0.176},
+      {2.05, {6.10, 2.60, 3.42}, 0.259, 0.221}},   // FP64 TM
+     {{2.03, {3.61, 2.73, 3.37}, 0.089, 0.230},
+      {2.20, {3.63, 2.63, 3.38}, 0.003, 0.312},
+      {0.00, {7.81, 5.94, 7.31}, 0.130, 0.457}},   // FP64 both
+    },
+    {
+     {{2.16, {2.45, 2.18, 2.38}, 0.152, 0.197},
+      {2.75, {2.06, 1.78, 2.20}, 0.091, 0.264},
+      {0.38, {4.81, 4.56, 5.47}, 0.251, 0.442},
+      {0.00, {13.02, 12.34, 13.38}, 0.949, 0.189}},   // FP32 TE
+     {{2.96, {1.74, 1.14, 1.22}, 0.167, 0.085},
+      {3.32, {1.47, 0.80, 0.95}, 0.098, 0.152},
+      {2.28, {3.17, 2.23, 2.40}, 0.251, 0.199},
+      {0.00, {11.32, 7.38, 7.96}, 0.592, 0.191}},   // FP32 TM
+     {{1.98, {2.53, 2.16, 2.49}, 0.122, 0.211},
+      {2.48, {2.25, 1.86, 2.27}, 0.071, 0.268},
+      {0.19, {5.28, 4.65, 5.51}, 0.206, 0.475},
+      {0.00, {13.34, 12.44, 13.20}, 0.960, 0.130}},   // FP32 both
+     {{1.11, {5.32, 4.98, 5.03}, 0.063, 0.371},
+      {0.97, {5.35, 5.00, 5.58}, 0.000, 0.468},
+      {0.00, {9.01, 8.50, 9.20}, 0.868, 0.000}},   // FP64 TE
+     {{2.90, {3.24, 2.12, 2.07}, 0.167, 0.217},
+      {2.99, {3.26, 2.08, 2.36}, 0.109, 0.207},
+      {0.00, {8.02, 6.00, 6.17}, 0.534, 0.069}},   // FP64 TM
+     {{1.00, {5.05, 4.48, 4.60}, 0.054, 0.411},
+      {0.71, {5.12, 4.57, 5.28}, 0.016, 0.474},
+      {0.00, {9.42, 8.75, 9.27}, 0.806, 0.000}},   // FP64 both
+    }};
 
 // workgroups per CU of a launch of n: whole ones while they are few
 double per_cu(double n) { return n <= 1024 ? std::ceil(n / 256) : n / 256 + 0.5; }
 
-double pass_us(const Fit &f, const Geo &g, int kind, int k, int64_t nx, int64_t ny)
+// workgroups per block of a pass
+int64_t tiles(const Geo &g, int kind, int k, int64_t nx, int64_t ny)
+{
+    const int W = g.rx - 2 * k - (kind == RK_FRONT ? 3 : 0), H = g.ry - 2 * k;
+    return ((nx + W - 1) / W) * ((ny + H - 1) / H);
+}
+
+double pass_us(const Fit &f, const Geo &g, int blocks, int kind, int k, int64_t nx, int64_t ny)
 {
     const int W = g.rx - 2 * k - (kind == RK_FRONT ? 3 : 0), H = g.ry - 2 * k;
     if (W < 12 || H < 4) return 1e30;
-    const double c = per_cu((double)((nx + W - 1) / W) * (double)((ny + H - 1) / H));
+    const double c = per_cu((double)tiles(g, kind, k, nx, ny) * (blocks == 3 ? 2 : 1));
     return f.t0 + c * f.load[kind] + k * (c * f.s + f.s0);
 }
 
@@ -79,8 +112,10 @@ constexpr int FX = 64, FYR = 16;
 // the (2p + 1)-tap binomial, y by p cascaded three-tap passes, the
 // operations of the row-streaming front in its order
 template <typename T, int P>
-__global__ __launch_bounds__(256) void k2_filter(int nx, int ny, int ntx, const T *s0, const T *s1, const T *s2, T *d0, T *d1, T *d2)
+__global__ __launch_bounds__(256) void k2_filter(int nx, int ny, int ntx, const T *s0, const T *s1, const T *s2, T *d0, T *d1, T *d2,
+                                                 const int *stall, int epoch)
 {
+    if (stall != nullptr && *stall == epoch) return;
     constexpr int RXJ = FX + 2 * P, RYJ = FYR + 2 * P;
     __shared__ T raw[RYJ][RXJ];
     __shared__ T fx[RYJ][FX];
@@ -114,27 +149,75 @@ __global__ __launch_bounds__(256) void k2_filter(int nx, int ny, int ntx, const 
     }
 }
 
+// E += dE of the blocks (those with sweeps) once all have finished, the
+// step's record, and B handed back; four cells per thread
+constexpr int FNT = 256, FPER = 4;
+template <typename T>
+__global__ __launch_bounds__(FNT) void k2_reg_finish(RegFinish<T> f)
+{
+    __shared__ RegTolBlock sb[2];
+    if (*f.tol.stall == f.tol.epoch) return;
+    const int w = threadIdx.x >> 6;
+    if (w < 2 && (f.blocks & (1 << w))) {
+        const RegTolBlock s = reg_tol_decide(f.tol, w);
+        if ((threadIdx.x & 63) == 0) {
+            sb[w] = s;
+            if (blockIdx.x == 0) f.tol.state[f.tol.par * 2 + w] = s;
+        }
+    }
+    __syncthreads();
+    SmallStat st{};
+    st.finished = 1;
+    const T *inc[3] = {nullptr, nullptr, nullptr};
+    const bool w0 = blockIdx.x == 0 && threadIdx.x == 0;
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        if (!(f.blocks & (1 << b))) continue;
+        const RegTolBlock s = sb[b];
+        st.done[b] = s.done;
+        st.conv[b] = s.conv;
+        st.resid[b] = s.resid;
+        st.rhsn[b] = s.rhsn;
+        st.nonfinite |= s.nonfinite;
+        if (!s.skip && s.done < f.target) st.finished = 0;
+#pragma unroll
+        for (int q = 0; q < 3; q++)
+            if ((q == 2) == (b == 1) && s.done > 0) inc[q] = s.last == 1 ? f.inc[1][q] : f.inc[0][q];
+    }
+    if (w0) {
+        *f.rec = st;
+        if (!st.finished || st.nonfinite) *f.stall = f.tol.epoch;
+    }
+    if (!st.finished || st.nonfinite) return;
+    const int64_t i0 = (int64_t)blockIdx.x * (FNT * FPER) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < FPER; u++) {
+        const int64_t i = i0 + u * FNT;
+        if (i >= f.n) return;
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            if (inc[q]) f.E[q][i] += ((gptr<const T>)inc[q])[i];
+            if (f.Bd[q]) f.Bd[q][i] = f.Bs[q][i];
+        }
+    }
+}
+
 }  // namespace reg2d
 
-RegPlan reg_plan(bool f64, int blocks, bool front, int64_t nx, int64_t ny, int m)
+RegPlan reg_plan(bool f64, int blocks, bool cheb, bool front, int64_t nx, int64_t ny, int m)
 {
     using namespace reg2d;
     RegPlan best{-1, 0, 1e29};
-    const Fit *fit = FIT[(f64 ? 3 : 0) + blocks - 1];
-    for (int g = 0; g < (blocks == 3 ? 3 : 4); g++) {
-        // FP64 workgroups of 128 columns hold a CU alone, so no second one
-        // hides their loads: 1500 x 1100, 8 sweeps, TE 72 against 41 us on
-        // 64 x 32 regions; where a CU has one workgroup only (1024^2, 20
-        // sweeps: 53 against 55) the wider region's smaller halo wins
-        if (f64 && g == 3 && nx * ny > (int64_t)5 << 18) continue;
-        const int kmax = (GEO[g].ry - 4) / 2;
+    const Fit *fit = FIT[cheb][(f64 ? 3 : 0) + blocks - 1];
+    for (int g = 0; g < (f64 ? 3 : 4); g++) {
+        const int kmax = std::min((GEO[g].ry - 4) / 2, 16);   // 16: the factor table of a pass
         const int n0 = std::max(front ? 2 : 1, (m + kmax - 1) / kmax);
         for (int n = n0; n <= n0 + 6; n++) {
             double t = 0.0;
             for (int i = 0, rem = m; i < n; i++) {
                 const int k = rem / (n - i);
                 const int kind = front && i == 0 ? RK_FRONT : (front && i == n - 1 ? RK_LAST : RK_MID);
-                t += pass_us(fit[g], GEO[g], kind, k, nx, ny);
+                t += pass_us(fit[g], GEO[g], blocks, kind, k, nx, ny);
                 rem -= k;
             }
             if (t < best.us) best = RegPlan{g, n, t};
@@ -143,30 +226,75 @@ RegPlan reg_plan(bool f64, int blocks, bool front, int64_t nx, int64_t ny, int m
     return best;
 }
 
-// Register tiles against row streams, us per step with current and filter at
-// 20 and at 8 sweeps.  FP32, both blocks: 1024^2 61 and 38 against 130 and
-// 67, 2048 x 1600 153 and 96 against 168 and 96, 2048^2 213 and 141 against
-// 201 and 113 (the fused streaming pass needs no second read of its halo):
-// up to 3.4 million cells.  One block, or FP64 (which streams each block on
-// its own): 2048^2 FP32 TE 112 and 70 against 133 and 76, FP64 both 388 and
-// 259 against 402 and 275, 2160^2 FP64 425 and 286 against 423 and 273: up to
-// 4.3 million.
-bool reg_pays(bool f64, int blocks, int64_t nx, int64_t ny)
+RegPlan reg_tol_plan(bool f64, int blocks, bool cheb, int64_t nx, int64_t ny, int k, int64_t stride)
 {
-    return nx * ny <= (!f64 && blocks == 3 ? (int64_t)13 << 18 : (int64_t)33 << 17);
+    using namespace reg2d;
+    RegPlan best{-1, 0, 1e29};
+    const Fit *fit = FIT[cheb][(f64 ? 3 : 0) + blocks - 1];
+    for (int g = 0; g < (f64 ? 3 : 4); g++) {
+        const int kmax = std::min((GEO[g].ry - 4) / 2, 16);   // 16: the factor table of a pass
+        const int n0 = (k + kmax - 1) / kmax;
+        for (int n = n0; n <= n0 + 1; n++) {
+            // two tested passes, the first with the front
+            double t = 0.0;
+            bool fits = true;
+            for (int i = 0; i < 2 * n; i++) {
+                const int kind = i == 0 ? RK_FRONT : RK_MID, kk = (k + n - 1) / n;
+                t += pass_us(fit[g], GEO[g], blocks, kind, kk, nx, ny);
+                fits = fits && tiles(GEO[g], kind, kk, nx, ny) <= stride;
+            }
+            if (fits && t < best.us) best = RegPlan{g, n, t};
+        }
+    }
+    return best;
+}
+
+// Register tiles against row streams, us per step.
+// Fixed counts (20 sweeps, current, filter), FP32: both blocks 1024^2 64
+// against 130, 2048 x 1600 163 against 178, 2048^2 217 against 202 (the fused
+// streaming pass reads its halo once): up to 3.4 million cells; TE 2048^2 114
+// against 133, 2560 x 2048 138 against 163, 4096 x 2048 234 against 206: 5.5
+// million.  FP64: both 2048^2 377 against 399, 2560 x 2048 465 against 451: 4.3
+// million; TM alone (streamed 12 sweeps deep) 2048 x 1600 132 against 147,
+// 2048^2 164 against 158: 3.4 million.
+// Tolerance solves: FP32 (two tested passes) 2048 x 1600 227 against 237,
+// 2048^2 286 against 286; FP64 (three) 379 against 436, 523 against 483: 3.4
+// million.
+// Chebyshev, 7 sweeps: FP32 1500 x 1100 70 against 93, 2048 x 1600 129 against
+// 120; FP64 131 against 141, 244 against 241: 2.2 million; its FP64 tolerance
+// solves (passes of four) 1024^2 301 against 356, 1500 x 1100 453 against 429:
+// 1.3 million.
+bool reg_pays(bool f64, int blocks, bool tol, bool cheb, int64_t nx, int64_t ny)
+{
+    int64_t most = (int64_t)13 << 18;
+    if (cheb) most = tol && f64 ? (int64_t)5 << 18 : (int64_t)17 << 17;
+    else if (!tol && f64 && blocks != 2) most = (int64_t)33 << 17;
+    else if (!tol && !f64 && blocks != 3) most = (int64_t)21 << 18;
+    return nx * ny <= most;
 }
 
 template <typename T>
-hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, const RegArgs<T> &a, hipStream_t s)
+hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, int form, bool tol, const RegArgs<T> &a, hipStream_t s,
+                      int *npart)
 {
-    if (blocks == 1) return reg2d::launch<T, 1>(c, geo, kind, a, s);
-    if (blocks == 2) return reg2d::launch<T, 2>(c, geo, kind, a, s);
-    if (blocks == 3) return reg2d::launch<T, 3>(c, geo, kind, a, s);
-    return hipErrorInvalidValue;
+    using namespace reg2d;
+    if (form == FM_STD) return tol ? launch<T, FM_STD, true>(c, blocks, geo, kind, a, s, npart) : launch<T, FM_STD, false>(c, blocks, geo, kind, a, s, npart);
+    if (form == FM_CHEB) return tol ? launch<T, FM_CHEB, true>(c, blocks, geo, kind, a, s, npart) : launch<T, FM_CHEB, false>(c, blocks, geo, kind, a, s, npart);
+    return tol ? launch<T, FM_DELTA, true>(c, blocks, geo, kind, a, s, npart) : hipErrorInvalidValue;
 }
 
 template <typename T>
-hipError_t launch_filter2d(const Coef<T> &c, int passes, int mask, const T *const J0[3], T *const out[3], hipStream_t s)
+hipError_t launch_reg_finish(const RegFinish<T> &f, hipStream_t s)
+{
+    using namespace reg2d;
+    const int64_t nb = (f.n + FNT * FPER - 1) / (FNT * FPER);
+    hipLaunchKernelGGL((k2_reg_finish<T>), dim3((unsigned)nb), dim3(FNT), 0, s, f);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_filter2d(const Coef<T> &c, int passes, int mask, const T *const J0[3], T *const out[3], const int *stall,
+                           int epoch, hipStream_t s)
 {
     using namespace reg2d;
     const int ntx = (c.nx + FX - 1) / FX;
@@ -174,18 +302,22 @@ hipError_t launch_filter2d(const Coef<T> &c, int passes, int mask, const T *cons
     T *d[3];
     for (int q = 0; q < 3; q++) d[q] = (mask >> q) & 1 ? out[q] : nullptr;
     switch (passes) {
-    case 1: hipLaunchKernelGGL((k2_filter<T, 1>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2]); break;
-    case 2: hipLaunchKernelGGL((k2_filter<T, 2>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2]); break;
-    case 3: hipLaunchKernelGGL((k2_filter<T, 3>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2]); break;
-    case 4: hipLaunchKernelGGL((k2_filter<T, 4>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2]); break;
+    case 1: hipLaunchKernelGGL((k2_filter<T, 1>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2], stall, epoch); break;
+    case 2: hipLaunchKernelGGL((k2_filter<T, 2>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2], stall, epoch); break;
+    case 3: hipLaunchKernelGGL((k2_filter<T, 3>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2], stall, epoch); break;
+    case 4: hipLaunchKernelGGL((k2_filter<T, 4>), grid, dim3(256), 0, s, c.nx, c.ny, ntx, J0[0], J0[1], J0[2], d[0], d[1], d[2], stall, epoch); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-template hipError_t launch_reg<float>(const Coef<float> &, int, int, int, const RegArgs<float> &, hipStream_t);
-template hipError_t launch_reg<double>(const Coef<double> &, int, int, int, const RegArgs<double> &, hipStream_t);
-template hipError_t launch_filter2d<float>(const Coef<float> &, int, int, const float *const[3], float *const[3], hipStream_t);
-template hipError_t launch_filter2d<double>(const Coef<double> &, int, int, const double *const[3], double *const[3], hipStream_t);
+#define MX_REG_INST(T)                                                                                                          \
+    template hipError_t launch_reg<T>(const Coef<T> &, int, int, int, int, bool, const RegArgs<T> &, hipStream_t, int *); \
+    template hipError_t launch_reg_finish<T>(const RegFinish<T> &, hipStream_t);
+MX_REG_INST(float)
+MX_REG_INST(double)
+#undef MX_REG_INST
+template hipError_t launch_filter2d<float>(const Coef<float> &, int, int, const float *const[3], float *const[3], const int *, int, hipStream_t);
+template hipError_t launch_filter2d<double>(const Coef<double> &, int, int, const double *const[3], double *const[3], const int *, int, hipStream_t);
 
 }  // namespace mx

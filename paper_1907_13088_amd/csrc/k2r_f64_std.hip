@@ -1,0 +1,8 @@
+// Instantiations of the register-tile passes: double, standard form, fixed counts.
+#include "k2r_impl.h"
+
+namespace mx {
+namespace reg2d {
+template hipError_t launch<double, FM_STD, false>(const Coef<double> &, int, int, int, const RegArgs<double> &, hipStream_t, int *);
+}  // namespace reg2d
+}  // namespace mx

@@ -163,9 +163,12 @@ struct mx_grid {
     int variant;          // 2D sweep kernel in use: 1 LDS tile, 2 row streaming (blocks
                           // together), 3 row streaming (each block on its own), 4 as 2
                           // with the front fused into the first pass where possible
-    bool reg = false;     // 2D, library choice: fixed counts of Alg 1 run on register tiles
+    bool reg = false;     // 2D, library choice: fixed counts run on register tiles
     RegPlan plan[2][3];   // their plans ([front][block set - 1]) for the counts plan_m
     int plan_m[2][3] = {{-1, -1, -1}, {-1, -1, -1}};
+    RegPlan tol_plan{-1, 0, 0.0};  // register tiles of a tolerance solve (geo < 0: not used)
+    int tol_stride = 0;       // norms per block and launch the workspace holds
+    int tol_passes = 1, tol_ahead = 1;   // tested passes per step, steps queued ahead of the host
     Coef<float> cf;
     Coef<double> cd;
     // Chebyshev solve: per block, the factors (previous increment, residual)
@@ -319,9 +322,17 @@ static void grid_setup(mx_grid *g, const mx_config *cfg, hipStream_t stream, int
         if (stream_workgroups(cfg, g->variant, cu) < cu / 2) g->variant = 1;
     }
     pass_depths(cfg, g->variant, g->spp);
-    // fixed counts on grids of up to a few million cells: register tiles
-    g->reg = cfg->ndim == 2 && cfg->variant == 0 && cfg->sweeps_per_pass == 0 && cfg->solver == MX_SOLVER_ALG1 &&
-             reg_pays(cfg->dtype == MX_F64, cfg->blocks, cfg->n[0], cfg->n[1]);
+    // grids of up to a few million cells: register tiles
+    const bool f64 = cfg->dtype == MX_F64, cheb = cfg->solver == MX_SOLVER_CHEBYSHEV;
+    const bool lib = cfg->ndim == 2 && cfg->variant == 0 && cfg->sweeps_per_pass == 0;
+    g->reg = lib && reg_pays(f64, cfg->blocks, false, cheb, cfg->n[0], cfg->n[1]);
+    if (lib && cfg->tol > 0.0 && !cfg->lumped && cfg->sweeps > 0 &&
+        reg_pays(f64, cfg->blocks, true, cheb, cfg->n[0], cfg->n[1])) {
+        // norms: three values per block and workgroup in the partial-sum buffer
+        g->tol_stride = (int)std::min<int64_t>(max_wg(cfg) / 3, 0x7fffffff);
+        g->tol_plan = reg_tol_plan(f64, cfg->blocks, cheb, cfg->n[0], cfg->n[1], g->spp[(cfg->blocks & 1) ? 0 : 1],
+                                   g->tol_stride);
+    }
     const size_t arr = up((size_t)g->ncell * elem_of(cfg));
     char *p = g->ws;
     auto take = [&](void **dst) { *dst = p; p += arr; };
@@ -467,6 +478,7 @@ int mx_init(const mx_config *cfg, void *stream, void *workspace, size_t workspac
     grid_setup(g, cfg, (hipStream_t)stream, attr.device, (char *)workspace, workspace_bytes);
     // pinned host memory: the tolerance solve reads its state back by DMA
     // rather than through a staged pageable copy
+    static_assert(4 * sizeof(RegTolBlock) <= ALIGN, "the state of a tolerance solve on register tiles fits its area");
     const size_t hbytes = std::max(sizeof(TolState), SMALL_MAX_STEPS * (sizeof(SmallStat) + sizeof(double)));
     if (hipHostMalloc((void **)&g->hred, hbytes, hipHostMallocDefault) != hipSuccess) {
         delete g;
@@ -774,26 +786,83 @@ const RegPlan &reg_plan_of(mx_grid *g, int blocks, bool front, int m)
 {
     RegPlan &p = g->plan[front][blocks - 1];
     if (g->plan_m[front][blocks - 1] != m) {
-        p = reg_plan(g->cfg.dtype == MX_F64, blocks, front, g->cfg.n[0], g->cfg.n[1], m);
+        p = reg_plan(g->cfg.dtype == MX_F64, blocks, g->cfg.solver == MX_SOLVER_CHEBYSHEV, front, g->cfg.n[0], g->cfg.n[1], m);
         g->plan_m[front][blocks - 1] = m;
     }
     return p;
 }
 
-// One solve on register tiles: with `front` (its E, B, Jf, env_src set) the
-// whole step including E += x, else x = sum_{j<count} A^j rhs left in
-// res[3].  Both blocks run in one set of passes when their counts agree and
-// that is modelled faster (FP64 tiles of both blocks hold few cells in
-// registers).
+// Buffers of the pass that reads iterate buffer cb (-1: the right-hand side
+// itself) and writes ob; the Chebyshev increments ping-pong with the iterate
+// (S, D2), the delta form's running sum stays in S
+template <typename T>
+void reg_buffers(const mx_grid *g, void *const rhs[3], int cb, int ob, bool cheb, RegArgs<T> &a)
+{
+    a.first = cb < 0;
+    for (int q = 0; q < 3; q++) {
+        a.dEp[q] = (T *)rhs[q];
+        a.rhs[q] = (const T *)rhs[q];
+        a.x_in[q] = (const T *)(cb < 0 ? rhs[q] : g->X[cb][q]);
+        a.x_out[q] = (T *)g->X[ob][q];
+        a.s_in[q] = (const T *)(cheb && cb == 1 ? g->D2[q] : g->S[q]);
+        a.s_out[q] = (T *)(cheb && ob == 1 ? g->D2[q] : g->S[q]);
+    }
+}
+
+// Chebyshev factors of a pass whose first sweep is sweep number `done`
+template <typename T>
+void reg_cheb(mx_grid *g, int done, RegArgs<T> &a)
+{
+    for (int b = 0; b < 2; b++)
+        for (int l = 0; l < a.k; l++)
+            for (int f = 0; f < 2; f++) {
+                const size_t ix = (size_t)(done + l);
+                a.cheb[b][f][l] = (T)(ix < g->cheb[b][f].size() ? g->cheb[b][f][ix] : 0.0);
+            }
+}
+
+// B of a step: the buffers its front reads and writes; the roles of the
+// stepped components swap
+template <typename T>
+void reg_swap_b(mx_grid *g, RegArgs<T> &a)
+{
+    for (int q = 0; q < 3; q++) {
+        a.Bin[q] = (const T *)(g->bloc[q] ? g->Bws[q] : g->B[q]);
+        a.B[q] = (T *)(g->bloc[q] ? g->B[q] : g->Bws[q]);
+        if (q == 2 ? (g->cfg.blocks & 1) : (g->cfg.blocks & 2)) g->bloc[q] ^= 1;
+    }
+}
+
+// Filter the current into `out` (the components of the stepped blocks); in a
+// queue of tolerance steps, unless it has stalled
+template <typename T>
+int reg_filter(mx_grid *g, void *const out[3], const int *stall = nullptr, int epoch = 0)
+{
+    const mx_config &c = g->cfg;
+    const int mask = ((c.blocks & 1) ? 3 : 0) | ((c.blocks & 2) ? 4 : 0);
+    ProfScope ps(g, MX_PROF_FRONT, (double)g->ncell * sizeof(T) * 2 * __builtin_popcount(mask));
+    HIPCHK(launch_filter2d<T>(coef<T>(g), c.filter_passes, mask, (const T *const *)g->J0, (T *const *)out, stall, epoch, g->stream));
+    return MX_OK;
+}
+
+// One solve on register tiles: with `front` (its E, B, env_src set) the whole
+// step including E += x, else x = P rhs left in res[3].  Blocks whose counts
+// agree run in one set of launches or one after the other, whichever is
+// modelled faster (on the largest grids one after the other keeps more of
+// their arrays in the last-level cache: 2048^2 FP64, 20 sweeps, 299 against
+// 340 us).
 template <typename T>
 int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int target[2], const T **res)
 {
     const mx_config &c = g->cfg;
     const Coef<T> &k = coef<T>(g);
+    const bool cheb = c.solver == MX_SOLVER_CHEBYSHEV;
+    if (cheb && (int)g->cheb[0][0].size() < std::max(target[0], target[1]))
+        fill_cheb(&c, std::max(target[0], target[1]), g->cheb);
     int groups[2] = {c.blocks & 1, c.blocks & 2};
+    const bool fr = front != nullptr;
     if (c.blocks == MX_ALL && target[0] == target[1] &&
-        reg_plan_of(g, 3, front != nullptr, target[0]).us <=
-            reg_plan_of(g, 1, front != nullptr, target[0]).us + reg_plan_of(g, 2, front != nullptr, target[1]).us) {
+        reg_plan_of(g, 3, fr, target[0]).us <= reg_plan_of(g, 1, fr, target[0]).us + reg_plan_of(g, 2, fr, target[0]).us) {
         groups[0] = 3;
         groups[1] = 0;
     }
@@ -803,29 +872,32 @@ int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int
         if (!blk) continue;
         const int m = target[blk == 2 ? 1 : 0];
         if (m == 0 && !front) continue;
-        const RegPlan &p = reg_plan_of(g, blk, front != nullptr, m);
+        const RegPlan &p = reg_plan_of(g, blk, fr, m);
         const int ncomp = blk == 3 ? 3 : (blk == 1 ? 2 : 1);
         const double arr = (double)g->ncell * sizeof(T);
+        // filtered current of the front: where the pass's own buffers leave
+        // room (the Chebyshev increments take S)
+        const bool filt = front && g->has_j && c.filter_passes > 0;
+        if (filt && cheb && p.passes > 2) {
+            const int rc = reg_filter<T>(g, g->X[1]);
+            if (rc) return rc;
+        }
         for (int i = 0, rem = m; i < p.passes; i++) {
             const int kind = front && i == 0 ? RK_FRONT : (front && i == p.passes - 1 ? RK_LAST : RK_MID);
             RegArgs<T> a = front ? *front : RegArgs<T>{};
             a.k = rem / (p.passes - i);
-            const int cb = (i - 1) & 1, ob = i & 1;
-            for (int q = 0; q < 3; q++) {
-                a.dEp[q] = (T *)rhs[q];
-                a.rhs[q] = (const T *)rhs[q];
-                a.x_in[q] = i == 0 ? (const T *)rhs[q] : (const T *)g->X[cb][q];
-                a.x_out[q] = (T *)g->X[ob][q];
-            }
+            const int ob = i & 1;
+            reg_buffers<T>(g, rhs, i == 0 ? -1 : ob ^ 1, ob, cheb, a);
+            if (cheb) reg_cheb<T>(g, m - rem, a);
             hipError_t e;
             {
                 // front: E, B, J read, B, dE', x written; others as the streaming passes
                 const int nb = blk == 3 ? 3 : (blk == 1 ? 1 : 2);
                 const int arrays = kind == RK_FRONT ? ncomp * (front->Jf[0] ? 4 : 3) + 2 * nb
-                                                    : ncomp * pass_arrays(false, false, !front && i == 0, kind == RK_LAST);
+                                                    : ncomp * pass_arrays(cheb, false, !front && i == 0, kind == RK_LAST);
                 ProfScope ps(g, kind == RK_FRONT ? MX_PROF_FRONT_SWEEP : kind == RK_LAST ? MX_PROF_SWEEP_LAST : MX_PROF_SWEEP,
                              arr * arrays);
-                e = launch_reg<T>(k, blk, p.geo, kind, a, g->stream);
+                e = launch_reg<T>(k, blk, p.geo, kind, cheb ? FM_CHEB : FM_STD, false, a, g->stream, nullptr);
             }
             if (e != hipSuccess) return fail(MX_EDEVICE, "register-tile pass: %s", hipGetErrorString(e));
             rem -= a.k;
@@ -837,19 +909,20 @@ int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int
     return MX_OK;
 }
 
-// nsteps steps of fixed counts of Alg 1 on register tiles
+// nsteps steps of fixed counts on register tiles
 template <typename T>
 int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_step_stats *stats)
 {
     const mx_config &c = g->cfg;
-    // the current's filter is the same at every step of the call: applied once
-    // (S is free: fixed counts keep no running sum)
+    // the current's filter is the same at every step of the call: applied
+    // once, into S (fixed counts of Alg 1 keep no running sum) or, for the
+    // Chebyshev solve, X[1] (free in steps of two passes; deeper ones filter
+    // each step, in reg_solve)
     void *const *Jf = g->J0;
     if (g->has_j && c.filter_passes > 0 && nsteps > 0) {
-        const int mask = ((c.blocks & 1) ? 3 : 0) | ((c.blocks & 2) ? 4 : 0);
-        ProfScope ps(g, MX_PROF_FRONT, (double)g->ncell * sizeof(T) * 2 * __builtin_popcount(mask));
-        HIPCHK(launch_filter2d<T>(coef<T>(g), c.filter_passes, mask, (const T *const *)g->J0, (T *const *)g->S, g->stream));
-        Jf = g->S;
+        Jf = c.solver == MX_SOLVER_CHEBYSHEV ? g->X[1] : g->S;
+        const int rc = reg_filter<T>(g, Jf);
+        if (rc) return rc;
     }
     for (int s = 0; s < nsteps; s++) {
         int target[2];
@@ -860,14 +933,12 @@ int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
         }
         RegArgs<T> a{};
         a.env_src = (T)((env ? env[s] : 0.0) * c.four_pi * c.dt);
+        reg_swap_b<T>(g, a);
         for (int q = 0; q < 3; q++) {
-            const bool act = q == 2 ? (c.blocks & 1) : (c.blocks & 2);
             a.E[q] = (T *)g->E[q];
             a.Jf[q] = g->has_j ? (const T *)Jf[q] : nullptr;
-            a.Bin[q] = (const T *)(g->bloc[q] ? g->Bws[q] : g->B[q]);
-            a.B[q] = (T *)(g->bloc[q] ? g->B[q] : g->Bws[q]);
-            if (act) g->bloc[q] ^= 1;
             // the call's last step hands B back in its last pass
+            const bool act = q == 2 ? (c.blocks & 1) : (c.blocks & 2);
             if (act && s == nsteps - 1 && g->bloc[q]) {
                 a.Bs[q] = (const T *)g->Bws[q];
                 a.Bd[q] = (T *)g->B[q];
@@ -881,6 +952,194 @@ int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
             for (int b = 0; b < 2; b++) stats[s].sweeps[b] = target[b];
         }
         g->step++;
+    }
+    return MX_OK;
+}
+
+// Tolerance solves on register tiles.  A step is a front pass with the first
+// tested pass's sweeps, further passes, and a finishing launch (the last
+// decision, E += dE, the step's record).  Every launch forms the stop
+// decision on the launch before it by itself, so steps are queued ahead of
+// the host: each with as many passes as the steps before it took; passes
+// after a block's stop do nothing.  A step that needs more passes than were
+// queued, or meets a norm that is not finite, stalls the queue: the launches
+// behind it do nothing and the host, which reads the records back once per
+// queue, goes on from there.  Sweep counts and iterates equal those of
+// testing after every pass on the host.
+template <typename T>
+int reg_tol_steps(mx_grid *g, int nsteps, const double *env, mx_step_stats *stats)
+{
+    const mx_config &c = g->cfg;
+    const Coef<T> &k = coef<T>(g);
+    const bool delta = c.form == MX_FORM_DELTA, cheb = c.solver == MX_SOLVER_CHEBYSHEV;
+    const int form = cheb ? FM_CHEB : delta ? FM_DELTA : FM_STD;
+    const int target = c.sweeps, spp = g->spp[(c.blocks & 1) ? 0 : 1];
+    if (cheb && (int)g->cheb[0][0].size() < target) fill_cheb(&c, target, g->cheb);
+    const RegPlan plan = g->tol_plan;
+    SmallStat *hs = g->hred ? (SmallStat *)g->hred : g->hstat;
+    int *stall = (int *)g->small_bar;
+    RegTol t0{};
+    t0.state = (RegTolBlock *)g->tol;
+    t0.norms = g->partial;
+    t0.stall = stall;
+    t0.tol = c.tol;
+    t0.stride = g->tol_stride;
+    t0.epoch = 1;
+    static const unsigned zero[4] = {0, 0, 0, 0};
+    HIPCHK(hipMemcpyAsync(stall, zero, sizeof(zero), hipMemcpyHostToDevice, g->stream));
+    const bool filt = g->has_j && c.filter_passes > 0;
+    const bool filt_step = filt && (delta || cheb);   // S is taken: X[1], rewritten by the second pass
+    void *const *Jf = !filt ? g->J0 : filt_step ? g->X[1] : g->S;
+    if (filt && !filt_step) {
+        const int rc = reg_filter<T>(g, Jf);
+        if (rc) return rc;
+    }
+    const int ncomp = c.blocks == 3 ? 3 : (c.blocks == 1 ? 2 : 1);
+    const double arr = (double)g->ncell * sizeof(T);
+    // launches of one step so far: parity of the chain, sweeps queued, and
+    // what the launch before left
+    struct Chain {
+        int n = 0, swe = 0, npart = 0, test = 0, kk = 0, buf = -1, front = 0;
+    } ch;
+    RegArgs<T> base{};   // the current step's
+    int bloc0[3];        // B locations before the current step
+    auto launch = [&](RegArgs<T> &a, int kind, int kk_pass, bool last_of_pass) -> int {
+        RegTol t = t0;
+        t.par = ch.n & 1;
+        t.npart = ch.npart;
+        t.init = ch.front;
+        t.test = ch.test;
+        t.kk = ch.kk;
+        t.buf = ch.buf;
+        t.res = last_of_pass ? 1 : 0;
+        a.tol = t;
+        const int ob = ch.buf == 0 ? 1 : 0;
+        reg_buffers<T>(g, g->dEp, ch.buf, ob, cheb, a);
+        if (cheb) reg_cheb<T>(g, ch.swe, a);
+        ProfScope ps(g, kind == RK_FRONT ? MX_PROF_FRONT_SWEEP : MX_PROF_SWEEP,
+                     arr * (kind == RK_FRONT ? 4 * ncomp + 3 : ncomp * pass_arrays(cheb, delta, false, false)));
+        const hipError_t e = launch_reg<T>(k, c.blocks, plan.geo, kind, form, true, a, g->stream, &ch.npart);
+        if (e != hipSuccess) return fail(MX_EDEVICE, "register-tile pass: %s", hipGetErrorString(e));
+        ch.n++;
+        ch.swe += a.k;
+        ch.front = kind == RK_FRONT;
+        ch.test = t.res;
+        ch.kk = kk_pass;
+        ch.buf = ob;
+        return MX_OK;
+    };
+    // queue one tested pass (its launches; the step's first begins with the front)
+    auto queue_pass = [&](bool front) -> int {
+        const int kk = std::min(spp, target - ch.swe);
+        const int nl = std::max(1, (kk * plan.passes + spp - 1) / spp);
+        for (int i = 0, rem = kk; i < nl; i++) {
+            RegArgs<T> a = base;
+            a.k = rem / (nl - i);
+            rem -= a.k;
+            const int rc = launch(a, front && i == 0 ? RK_FRONT : RK_MID, kk, i == nl - 1);
+            if (rc) return rc;
+        }
+        return MX_OK;
+    };
+    auto finish = [&](int rec, bool last_step) -> int {
+        RegFinish<T> f{};
+        RegTol t = t0;
+        t.par = ch.n & 1;
+        t.npart = ch.npart;
+        t.init = ch.front;
+        t.test = ch.test;
+        t.kk = ch.kk;
+        t.buf = ch.buf;
+        f.tol = t;
+        for (int q = 0; q < 3; q++) {
+            f.E[q] = (T *)g->E[q];
+            for (int b = 0; b < 2; b++) f.inc[b][q] = (const T *)(delta ? g->S[q] : g->X[b][q]);
+            if (last_step && g->bloc[q]) {
+                f.Bs[q] = (const T *)g->Bws[q];
+                f.Bd[q] = (T *)g->B[q];
+            }
+        }
+        f.rec = g->small_stat + rec;
+        f.stall = stall;
+        f.n = g->ncell;
+        f.blocks = c.blocks;
+        f.target = target;
+        ProfScope ps(g, MX_PROF_OTHER, arr * 3 * ncomp);
+        HIPCHK(launch_reg_finish<T>(f, g->stream));
+        ch.n++;
+        ch.front = ch.test = 0;
+        return MX_OK;
+    };
+    int s = 0;
+    bool resume = false;   // the step s has its front and some passes behind it
+    Chain resume_ch;
+    while (s < nsteps) {
+        const int n = std::min({nsteps - s, std::max(1, g->tol_ahead), SMALL_MAX_STEPS});
+        int locs[SMALL_MAX_STEPS + 1][3];   // B locations before each queued step
+        Chain chains[SMALL_MAX_STEPS];
+        for (int i = 0; i < n; i++) {
+            for (int q = 0; q < 3; q++) locs[i][q] = g->bloc[q];
+            int rc = MX_OK;
+            if (i == 0 && resume) {
+                ch = resume_ch;
+                for (int q = 0; q < 3; q++) locs[i][q] = bloc0[q];
+                rc = queue_pass(false);
+            } else {
+                ch = Chain{};
+                base = RegArgs<T>{};
+                base.env_src = (T)((env ? env[s + i] : 0.0) * c.four_pi * c.dt);
+                reg_swap_b<T>(g, base);
+                for (int q = 0; q < 3; q++) {
+                    base.E[q] = (T *)g->E[q];
+                    base.Jf[q] = g->has_j ? (const T *)Jf[q] : nullptr;
+                }
+                if (filt_step) rc = reg_filter<T>(g, Jf, stall, t0.epoch);
+                for (int p = 0; rc == MX_OK && p < g->tol_passes && ch.swe < target; p++) rc = queue_pass(p == 0);
+            }
+            if (rc == MX_OK) rc = finish(i, s + i == nsteps - 1);
+            if (rc) return rc;
+            chains[i] = ch;
+        }
+        for (int q = 0; q < 3; q++) locs[n][q] = g->bloc[q];
+        HIPCHK(hipMemcpyAsync(hs, g->small_stat, n * sizeof(SmallStat), hipMemcpyDeviceToHost, g->stream));
+        HIPCHK(hipStreamSynchronize(g->stream));
+        int i = 0, most = 1;
+        for (; i < n; i++) {
+            const SmallStat &r = hs[i];
+            most = std::max(most, (std::max(r.done[0], r.done[1]) + spp - 1) / spp);
+            if (r.nonfinite || !r.finished) break;
+            if (stats) {
+                mx_step_stats &st = stats[s + i];
+                for (int b = 0; b < 2; b++) {
+                    st.sweeps[b] = r.done[b];
+                    st.resid[b] = r.resid[b];
+                    st.rhs[b] = r.rhsn[b];
+                    st.nonconverged[b] = (c.blocks & (1 << b)) && r.done[b] > 0 && !r.conv[b] ? 1 : 0;
+                }
+            }
+            g->step++;
+        }
+        s += i;
+        resume = false;
+        if (i < n) {
+            // step s stalled: B of the steps behind it did not move
+            for (int q = 0; q < 3; q++) g->bloc[q] = locs[i + 1][q];
+            if (hs[i].nonfinite)
+                return fail(MX_ENONFINITE, hs[i].nonfinite & 1 ? "step %lld: norm of dE' is not finite" : "step %lld: a residual norm is not finite",
+                            (long long)g->step);
+            resume = true;
+            resume_ch = chains[i];
+            for (int q = 0; q < 3; q++) bloc0[q] = locs[i][q];
+            t0.epoch++;
+            // one pass more than it had
+            g->tol_passes = std::max(g->tol_passes, (chains[i].swe + spp - 1) / spp + 1);
+            g->tol_ahead = std::max(1, g->tol_ahead / 4);
+        } else {
+            g->tol_passes = most;
+            g->tol_ahead = std::min(SMALL_MAX_STEPS, g->tol_ahead * 2);
+            if (s == nsteps)   // the last finishing launch handed B back
+                for (int q = 0; q < 3; q++) g->bloc[q] = 0;
+        }
     }
     return MX_OK;
 }
@@ -1071,11 +1330,18 @@ int step_impl(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
     const Coef<T> &k = coef<T>(g);
     const int nblk = c.ndim == 3 ? 1 : 2;
     const bool tolmode = c.tol > 0.0 && replay == nullptr;
-    if (tolmode && nsteps > 0 && small_ok<T>(g)) {
+    if (tolmode && nsteps > 0 && g->tol_plan.geo >= 0) {
+        const int rc = reg_tol_steps<T>(g, nsteps, env, stats);
+        if (rc) return rc;
+        nsteps = 0;
+    } else if (tolmode && nsteps > 0 && small_ok<T>(g)) {
         const int rc = small_steps<T>(g, nsteps, env, stats);
         if (rc) return rc;
         nsteps = 0;   // done; the hand-back below returns B to the caller's buffers
-    } else if (g->reg && !tolmode) {
+    } else if (g->reg && !tolmode &&
+               (nsteps >= 8 || g->ncell <= REG_FEW || !g->has_j || c.filter_passes == 0)) {
+        // (the filter runs apart here, once per call: on the larger grids it
+        // would cost short calls what the tiles gain, 30 us at 2048^2 FP64)
         const int rc = reg_steps<T>(g, nsteps, env, replay, stats);
         if (rc) return rc;
         nsteps = 0;

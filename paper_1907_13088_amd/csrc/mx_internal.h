@@ -232,8 +232,51 @@ bool front_sweep2d_ok(bool f64, int k, int filter_passes);
 template <typename T>
 hipError_t launch_front_sweep2d(const Coef<T> &c, int filter_passes, int k, const FrontArgs<T> &fa,
                                 const T *const Bin[3], const SweepArgs<T> &sa, hipStream_t s, int *nwg);
+// Record of a step of a tolerance solve run ahead of the host
+constexpr int SMALL_MAX_STEPS = 64;
+struct SmallStat {
+    int done[2];          // sweeps per block (TE, TM)
+    int conv[2];          // met the tolerance
+    double resid[2];      // last step norm per block
+    double rhsn[2];       // ||dE'|| per block
+    int nonfinite;        // bit 0: ||dE'||, bit 1: a residual
+    int finished;         // every block converged or at its count (register tiles)
+};
 // Register-tile passes for grids too small for row streams (k2r_impl.h)
 enum : int { RK_FRONT = 0, RK_MID = 1, RK_LAST = 2 };   // kinds of pass
+// Tolerance solve: a block's state between the launches of a step
+struct RegTolBlock {
+    double rhsn, resid;   // ||dE'||, ||x_(j+1) - x_j|| of the last tested pass
+    int done, conv;       // sweeps run; met resid <= tol rhsn
+    int skip, last;       // further passes do nothing; iterate buffer of the last tested pass (-1: none)
+    int nonfinite, pad;   // 1: ||dE'||, 2: a residual
+};
+struct RegTol {
+    RegTolBlock *state;       // [2][2]: by parity of the launch, then block
+    double *norms;            // [3][2][stride]: dE', then the steps by parity of the launch
+    const int *stall;         // equal to epoch: do nothing
+    double tol;
+    int epoch, stride;
+    int par;                  // parity of this launch
+    int npart;                // workgroups per block of the launch before
+    int init, test;           // it was the front (rhsn is to be formed); it ended a tested pass
+    int kk, buf;              // the tested pass's sweeps and iterate buffer
+    int res;                  // this launch ends a tested pass
+};
+// End of a tolerance step: the last decision, then E += dE of every block, if
+// all have finished, and the step's record; else the queue stalls
+template <typename T>
+struct RegFinish {
+    T *E[3];
+    const T *inc[2][3];       // the increment, by iterate buffer (delta form: the running sum)
+    const T *Bs[3];           // B handed back (null: none)
+    T *Bd[3];
+    RegTol tol;
+    SmallStat *rec;
+    int *stall;
+    int64_t n;
+    int blocks, target;
+};
 template <typename T>
 struct RegArgs {
     T *E[3];              // front: E^n, read; last pass: E += x
@@ -244,26 +287,40 @@ struct RegArgs {
     T *dEp[3];            // front: dE' out
     const T *rhs[3];      // other passes: dE'
     const T *x_in[3];     // other passes: the iterate (rhs on the first pass)
+    const T *s_in[3];     // running sum (delta form), increment (Chebyshev)
     T *x_out[3];          // passes that store the iterate
+    T *s_out[3];
     const T *Bs[3];       // last pass: B handed back, Bd = Bs on the own cells (null: none)
     T *Bd[3];
+    int first;            // no sweeps before this pass (no running sum or increment to read)
     int k;                // sweeps
+    T cheb[2][2][16];     // Chebyshev form: per block and sweep of the pass, the factors
+    RegTol tol;
 };
 // How one solve of m sweeps of a block set is cut: the tile geometry and the
-// number of passes (front + others when `front`, else passes without one);
-// geo < 0: no plan
+// number of passes (front + others when `front`, else passes without one)
 struct RegPlan {
     int geo, passes;
     double us;            // modelled time
 };
-RegPlan reg_plan(bool f64, int blocks, bool front, int64_t nx, int64_t ny, int m);
+RegPlan reg_plan(bool f64, int blocks, bool cheb, bool front, int64_t nx, int64_t ny, int m);
+// geometry of a tolerance solve whose tested passes have k sweeps, in
+// launches of nearly equal depth, with at most `stride` workgroups per block
+// (geo < 0: none); passes: launches of a tested pass
+RegPlan reg_tol_plan(bool f64, int blocks, bool cheb, int64_t nx, int64_t ny, int k, int64_t stride);
 // grids that the register tiles step faster than the row streams do
-bool reg_pays(bool f64, int blocks, int64_t nx, int64_t ny);
+bool reg_pays(bool f64, int blocks, bool tol, bool cheb, int64_t nx, int64_t ny);
+constexpr int64_t REG_FEW = (int64_t)17 << 17;   // cells up to which they do in calls of a few steps too (the filter runs apart)
 template <typename T>
-hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, const RegArgs<T> &a, hipStream_t s);
-// out = p binomial passes per axis of the components of mask (2D)
+hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, int form, bool tol, const RegArgs<T> &a, hipStream_t s,
+                      int *npart);
 template <typename T>
-hipError_t launch_filter2d(const Coef<T> &c, int passes, int mask, const T *const J0[3], T *const out[3], hipStream_t s);
+hipError_t launch_reg_finish(const RegFinish<T> &f, hipStream_t s);
+// out = p binomial passes per axis of the components of mask (2D); nothing
+// where *stall equals epoch (stall null: always)
+template <typename T>
+hipError_t launch_filter2d(const Coef<T> &c, int passes, int mask, const T *const J0[3], T *const out[3], const int *stall,
+                           int epoch, hipStream_t s);
 
 template <typename T>
 hipError_t launch_update(int64_t n, int comp_mask, T *const E[3], const T *const X[3], hipStream_t s);
@@ -277,15 +334,6 @@ int step_on_scratch(const mx_config *cfg, void *stream, int device, void *ws, si
 // Single-launch tolerance solve of small 2D grids (k2small_impl.h): all
 // passes of up to SMALL_MAX_STEPS steps in one cooperative launch, the stop
 // test on the device, one read-back of the per-step records per launch.
-constexpr int SMALL_MAX_STEPS = 64;
-struct SmallStat {
-    int done[2];          // sweeps per block (TE, TM)
-    int conv[2];          // met the tolerance
-    double resid[2];      // last step norm per block
-    double rhsn[2];       // ||dE'|| per block
-    int nonfinite;        // bit 0: ||dE'||, bit 1: a residual
-    int pad;
-};
 template <typename T>
 struct SmallArgs {
     Coef<T> c;

@@ -121,3 +121,100 @@ def test_a_caller_stream_and_graph_replays():
             assert torch.equal(x, y)
     g.close()
     g2.close()
+
+
+def _tol(n, dtype, m, steps, spp, variant, tol, p=1, form=0, solver=0, blocks=mx.MX_ALL, replay=None, scale=None):
+    import torch
+    g = mx.Grid(mx.make_config(2, n, 0.35, (1.0, 1.0), dtype, blocks, m, 0.0 if replay else tol, p, form=form, solver=solver,
+                               sweeps_per_pass=spp, variant=variant))
+    f = _rand((n[1], n[0]), dtype, 5, 9)
+    g.bind(f[:3], f[3:6])
+    g.set_current(f[6:])
+    st, at = [], 0
+    env = [1.0 if scale is None else scale[s] for s in range(sum(steps))]
+    for k in steps:
+        st += g.step(k, env=env[at:at + k], replay=None if replay is None else replay[at:at + k], stats=True)
+        at += k
+    torch.cuda.synchronize()
+    k = g.block_sweeps_per_pass
+    g.close()
+    return f[:6], st, k
+
+
+@pytest.mark.parametrize("dtype,form,solver,tol", [("f64", 0, 0, 1e-9), ("f32", 1, 0, 1e-6), ("f64", 1, 0, 1e-9),
+                                                   ("f32", 0, 1, 1e-5), ("f64", 0, 1, 1e-9)])
+@pytest.mark.parametrize("n,blocks", [((3, 2), 3), ((64, 32), 3), ((129, 65), 1), ((200, 136), 2), ((900, 500), 3),
+                                      ((1030, 1000), 3)])
+def test_tolerance_solves_equal_the_other_kernels(n, blocks, dtype, form, solver, tol):
+    """Queued ahead of the host, with counts that differ between the blocks and
+    rise and fall from step to step (the current's envelope jumps): the same
+    counts, converged flags and bitwise the same fields as the per-launch
+    kernels at the same pass depth."""
+    scale = [0.0, 1e-3, 30.0, 1e-6, 1.0, 1.0, 1.0, 1.0, 1e3, 0.0]
+    steps = (1, 5, 4)
+    a = _tol(n, dtype, 300, steps, 0, 0, tol, form=form, solver=solver, blocks=blocks, scale=scale)
+    spp = a[2][0]
+    b = _tol(n, dtype, 300, steps, spp, 3 if solver else 1, tol, form=form, solver=solver, blocks=blocks, scale=scale)
+    assert a[2] == b[2]
+    for s, t in zip(a[1], b[1]):
+        assert s.sweeps == t.sweeps and s.nonconverged == t.nonconverged
+        # the norms are summed in another order
+        assert s.rhs == pytest.approx(t.rhs, rel=1e-12) and s.resid == pytest.approx(t.resid, rel=1e-9)
+    _same((a[0], None), (b[0], None), (n, dtype, form, solver))
+
+
+def test_tolerance_solve_ends_at_the_count():
+    """m_max between multiples of the pass depth: the last pass is shorter and
+    the step is flagged."""
+    for m in (1, 9, 20):
+        a = _tol((150, 90), "f64", m, (3,), 0, 0, 1e-14)
+        b = _tol((150, 90), "f64", m, (3,), a[2][0], 1, 1e-14)
+        assert [s.sweeps for s in a[1]] == [(m, m)] * 3 and all(s.nonconverged == (1, 1) for s in a[1])
+        _same((a[0], None), (b[0], None), m)
+
+
+def test_zero_fields_take_no_sweeps():
+    import torch
+    g = mx.Grid(mx.make_config(2, (70, 50), 0.35, (1.0, 1.0), "f64", mx.MX_ALL, 50, 1e-9))
+    f = [torch.zeros((50, 70), dtype=torch.float64, device="cuda") for _ in range(6)]
+    g.bind(f[:3], f[3:])
+    st = g.step(3, stats=True)
+    assert all(s.sweeps == (0, 0) and s.nonconverged == (0, 0) for s in st)
+    assert all(not t.any() for t in f)
+    g.close()
+
+
+def test_nonfinite_step_stops_the_queue():
+    """A norm that stops being finite in the middle of queued steps: the error
+    names its step, and the steps before it are done."""
+    import torch
+    g = mx.Grid(mx.make_config(2, (100, 60), 0.35, (1.0, 1.0), "f64", mx.MX_ALL, 50, 1e-9, 0))
+    f = _rand((60, 100), "f64", 2, 9)
+    g.bind(f[:3], f[3:6])
+    g.set_current(f[6:])
+    g.step(8, env=[1.0] * 8)
+    with pytest.raises(mx.MxError) as ei:
+        g.step(6, env=[1.0, 1.0, 1.0, float("inf"), 1.0, 1.0])
+    assert ei.value.code == mx.MX_ENONFINITE and "step 11:" in str(ei.value)
+    assert g.step_count == 11
+    torch.cuda.synchronize()
+    assert all(torch.isfinite(t).all() for t in f[:3])
+    g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_chebyshev_counts(dtype):
+    for n, m, p, blocks in (((210, 90), 7, 3, 3), ((1, 1), 3, 0, 3), ((333, 120), 29, 2, 3), ((500, 700), 10, 1, 1),
+                            ((129, 65), 1, 4, 2), ((333, 120), 0, 1, 3)):
+        out = []
+        for variant in (0, 3):
+            g = mx.Grid(mx.make_config(2, n, 0.4, (1.0, 1.0), dtype, blocks, m, 0.0, p, variant=variant, solver=1))
+            f = _rand((n[1], n[0]), dtype, 9, 9)
+            g.bind(f[:3], f[3:6])
+            g.set_current(f[6:])
+            st = g.step(3, env=[0.3, 1.0, -0.5], stats=True)
+            e, b = _rand((n[1], n[0]), dtype, 10, 3), _rand((n[1], n[0]), dtype, 12, 3)
+            g.adjoint(1, [0.5], [(m, m)], e, b, f[6:])
+            g.close()
+            out.append((f + e + b, [s.sweeps for s in st]))
+        _same(out[0], out[1], (n, m, dtype))
