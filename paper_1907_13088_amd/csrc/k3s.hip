@@ -15,18 +15,34 @@
 // in the same order, ((from p - 1) + (from p)) + (from p + 1), whatever the
 // pass depth, so passes of any depth give bitwise identical iterates.
 //
-// A workgroup of TX x TYT threads owns a column tile of TX x TY (TY = R TYT;
-// each thread carries R consecutive rows, which share their neighbours'
-// LDS reads).  Level l (1..K) computes plane t - 2l at march step t from
-// the planes of level l - 1 that arrived at earlier steps (one barrier per
-// step), and hands its newest plane to level l + 1 through a
-// double-buffered LDS plane.  The valid columns shrink by one per level on
-// each side, so a tile writes (TX - 2(K - 1)) x (TY - 2(K - 1)) columns;
-// the level-0 plane is loaded with a one-cell ring.  The carried value (dE'
-// in the standard form, the running sum in the delta form, dE' and the
-// increment in the Chebyshev form) travels with the planes.
+// A workgroup of NW waves owns a column tile of 64 x TY (TY = R NW): lane =
+// x column, wave w carries rows w R .. w R + R - 1 in registers.  Level l
+// (1..K) computes plane t - 2l at march step t from the planes of level
+// l - 1 that arrived at earlier steps (one barrier per step).  Neighbours
+// across x come from the neighbouring lanes, rows above and below from the
+// wave's own registers; LDS carries only the first and last row of each
+// wave, in a buffer per level and parity.  The valid columns shrink by one
+// per level on each side; along y the level-0 plane is loaded with one row
+// more on each side.  So a tile writes (64 - 2K) x (TY - 2(K - 1)) columns.
+// The carried value (dE' in the standard form, the running sum in the delta
+// form, dE' and the increment in the Chebyshev form) is read when level 1
+// completes a plane and then travels with the planes.
+//
+// What bounds it: VALU issue and, with the 8 to 16 waves that fit a CU, the
+// latencies between two barriers (512^3, FP32, three sweeps: 61 % of the VALU
+// cycles; the HBM traffic alone would take half the time).  Rows in registers
+// instead of planes in LDS take a quarter of the VALU and nine tenths of the
+// LDS instructions away against a kernel that reads the 3 x 3 columns of each
+// point from LDS, which measured, per pass: 512^3 FP32 delta form 2.11 ms
+// against 1.93 now, FP32 Alg 1 1.69 against 1.40 (ten sweeps, front taken
+// off), 256^3 FP64 0.38 against 0.32, Chebyshev FP64 at 250^3 8.64 ms per
+// step against 7.19.  The tile is 58 instead of 60 columns wide in FP32 with
+// three sweeps (60 instead of 62 in FP64 with two): where the grid's width is a
+// multiple of the wider tile only, the pass gains little or loses (180^3
+// FP32 Chebyshev: 1.12 ms per step against 1.19).
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "mx_internal.h"
 #include "stencil2d.h"
@@ -83,29 +99,61 @@ __device__ __forceinline__ T avg6(T fm, T f0, T fp)
     return fmad(d2(fm, f0, fp), T(1.0 / 6.0), f0);
 }
 
-// v[dj + 1][di + 1]: the 3 x 3 neighbourhood of the column
-template <typename T>
-__device__ __forceinline__ Q<T> inplane(const P3<T> (&v)[3][3])
+// value of the lane one column to the left or right (zero at the tile's edge,
+// in columns that no output needs)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
 {
-    auto X = [&](int di, int dj) { return v[dj + 1][di + 1].x; };
-    auto Y = [&](int di, int dj) { return v[dj + 1][di + 1].y; };
-    auto Z = [&](int di, int dj) { return v[dj + 1][di + 1].z; };
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    const long long u = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+template <typename T>
+__device__ __forceinline__ T from_left(T v) { return dpp<0x138>(v); }    // wave_shr:1, lane - 1
+template <typename T>
+__device__ __forceinline__ T from_right(T v) { return dpp<0x130>(v); }   // wave_shl:1, lane + 1
+
+// one row of a plane: its values and the differences along x that the rows
+// above and below it use too
+template <typename T>
+struct Row {
+    P3<T> v;
+    T dx, dz, lxx;   // Dx' X (backward), Dx Z (forward), Dxx Z
+};
+
+template <typename T>
+__device__ __forceinline__ Row<T> row_of(const P3<T> &v)
+{
+    const T zr = from_right(v.z);
+    return Row<T>{v, v.x - from_left(v.x), zr - v.z, d2(from_left(v.z), v.z, zr)};
+}
+
+// the quantities of the middle one of three rows
+template <typename T>
+__device__ __forceinline__ Q<T> inplane(const Row<T> &m, const Row<T> &c, const Row<T> &p)
+{
     Q<T> q;
-    q.X = X(0, 0);
-    q.Y = Y(0, 0);
-    q.Z = Z(0, 0);
-    q.lyyx = d2(X(0, -1), q.X, X(0, 1));
-    q.pxy = (Y(1, 0) - Y(1, -1)) - (q.Y - Y(0, -1));
-    q.rxz = avg6(Z(1, -1) - Z(0, -1), Z(1, 0) - q.Z, Z(1, 1) - Z(0, 1));
-    q.lxxy = d2(Y(-1, 0), q.Y, Y(1, 0));
-    q.pyx = (X(0, 1) - X(-1, 1)) - (q.X - X(-1, 0));
-    q.ryz = avg6(Z(-1, 1) - Z(-1, 0), Z(0, 1) - q.Z, Z(1, 1) - Z(1, 0));
-    const T lxm = d2(Z(-1, -1), Z(0, -1), Z(1, -1)), lxp = d2(Z(-1, 1), Z(0, 1), Z(1, 1));
-    q.lxxz = d2(Z(-1, 0), q.Z, Z(1, 0));
-    q.lyyz = d2(Z(0, -1), q.Z, Z(0, 1));
-    q.lxyz = d2(lxm, q.lxxz, lxp);
-    q.szx = avg6(X(0, -1) - X(-1, -1), q.X - X(-1, 0), X(0, 1) - X(-1, 1));
-    q.szy = avg6(Y(-1, 0) - Y(-1, -1), q.Y - Y(0, -1), Y(1, 0) - Y(1, -1));
+    q.X = c.v.x;
+    q.Y = c.v.y;
+    q.Z = c.v.z;
+    const T dy = c.v.y - m.v.y, dyz = p.v.z - c.v.z, dyr = from_right(dy);
+    q.lyyx = d2(m.v.x, c.v.x, p.v.x);
+    q.pxy = dyr - dy;
+    q.rxz = avg6(m.dz, c.dz, p.dz);
+    q.lxxy = d2(from_left(c.v.y), c.v.y, from_right(c.v.y));
+    q.pyx = p.dx - c.dx;
+    q.ryz = avg6(from_left(dyz), dyz, from_right(dyz));
+    q.lxxz = c.lxx;
+    q.lyyz = d2(m.v.z, c.v.z, p.v.z);
+    q.lxyz = d2(m.lxx, c.lxx, p.lxx);
+    q.szx = avg6(m.dx, c.dx, p.dx);
+    q.szy = avg6(from_left(dy), dy, dyr);
     return q;
 }
 
@@ -134,201 +182,228 @@ __device__ __forceinline__ void setc(P3<T> &p, int q, T v)
 
 // FORM: FM_STD (x_l = b + A x_(l-1)), FM_DELTA (d_l = A d_(l-1), s_l = s_(l-1)
 // + d_l) or FM_CHEB (r = b + A x - x, d_l = f_l d_(l-1) + g_l r, x_l = x + d_l).
-template <typename T, int K, int FORM, int TX, int TYT, int R>
-__global__ __launch_bounds__(TX *TYT) void k3_stream(Coef<T> c, Zc<T> z, SweepArgs<T> a, int flags, int Lz)
+template <typename T, int K, int FORM, bool LAST, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepArgs<T> a, int flags, int Lz)
 {
     constexpr bool DELTA = FORM == FM_DELTA, CHEB = FORM == FM_CHEB;
-    constexpr int NTH = TX * TYT, TY = TYT * R, LX = TX + 2, LY = TY + 2;
-    constexpr int RING = 2 * (LX + TY), RPER = (RING + NTH - 1) / NTH;
+    // rows at the waves' edges in LDS, EDGE per wave: wave w's first row in
+    // slot EDGE w + 1, its last in slot EDGE w + EDGE; the first and the last
+    // slot hold the rows around the tile (level 0 only)
+    constexpr int TY = NW * R, EDGE = R > 1 ? 2 : 1, SLOTS = EDGE * NW + 2;
+    static_assert(NW >= 2, "the first and the last wave load one row more each");
     if (a.skip && *a.skip) return;   // the solve has met its stop test
-    __shared__ P3<T> pl[K][2][LY][LX];   // [level][parity][y][x]
-    __shared__ double sred[NTH / 64];
+    __shared__ T pl[K][2][SLOTS][3][64];   // [level][parity][slot][component][x]
+    __shared__ double sred[NW];
     const int nx = c.nx, ny = c.ny, nz = c.nz;
-    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwg = gridDim.x * gridDim.y * gridDim.z;
     const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const int tl = xcd_map(lin, nwg);
     const int gxy = gridDim.x * gridDim.y;
-    constexpr int OX = TX - 2 * (K - 1), OY = TY - 2 * (K - 1);   // output columns of a tile
+    constexpr int OX = 64 - 2 * K, OY = TY - 2 * (K - 1);   // output columns of a tile
     const int X0 = (tl % gridDim.x) * OX, Y0 = ((tl % gxy) / gridDim.x) * OY;
     const int Z0 = (tl / gxy) * Lz, Z1 = min(nz, Z0 + Lz);
     const size_t plane = (size_t)nx * ny;
-    // own columns: x = ux, rows uy0 + r, LDS rows ly0 + r
-    const int ux = X0 - (K - 1) + tx, ly0 = 1 + ty * R, uy0 = Y0 - (K - 1) + ty * R;
-    size_t own[R];
-    bool outc[R];
+    // own columns: x = ux, rows uy0 + r.  Plane and row are the same for a
+    // wave, so each row of an array is a buffer with a scalar base, and the
+    // lane's offset along x serves all of them.  An offset past the row's
+    // end drops a store, without a branch: every step issues the same
+    // memory operations, and the wait for a load leaves later stores alone.
+    const int ux = X0 - K + lane, uy0 = Y0 - (K - 1) + w * R;
+    constexpr unsigned DROP = BUF_DROP;
+    const unsigned row_bytes = (unsigned)nx * (unsigned)sizeof(T);
+    const unsigned xin_off = (unsigned)wrapm(ux, nx) * (unsigned)sizeof(T);
+    const unsigned xout_off = lane >= K && lane < 64 - K && ux < nx ? xin_off : DROP;
+    size_t row[R];
+    bool outy[R];
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        own[r] = (size_t)wrapm(uy0 + r, ny) * nx + wrapm(ux, nx);
-        const int iy = ty * R + r;
-        outc[r] = tx >= K - 1 && tx < TX - (K - 1) && iy >= K - 1 && iy < TY - (K - 1) && ux < nx && uy0 + r < ny;
+        row[r] = (size_t)wrapm(uy0 + r, ny) * nx;
+        const int iy = w * R + r;
+        outy[r] = iy >= K - 1 && iy < TY - (K - 1) && uy0 + r < ny;
     }
-    // ring cells of the level-0 plane this thread loads
-    size_t roff[RPER];
-    int rcx[RPER], rcy[RPER];
-#pragma unroll
-    for (int u = 0; u < RPER; u++) {
-        const int rr = tid + u * NTH;
-        int cx = -1, cy = -1;
-        if (rr < RING) {
-            if (rr < LX) { cx = rr; cy = 0; }
-            else if (rr < 2 * LX) { cx = rr - LX; cy = LY - 1; }
-            else if (rr < 2 * LX + TY) { cx = 0; cy = rr - 2 * LX + 1; }
-            else { cx = LX - 1; cy = rr - 2 * LX - TY + 1; }
-        }
-        rcx[u] = cx;
-        rcy[u] = cy;
-        roff[u] = cx < 0 ? 0 : (size_t)wrapm(Y0 - K + cy, ny) * nx + wrapm(X0 - K + cx, nx);
-    }
-    const bool first = flags & SW_FIRST;
-    const T *xin[3], *cin[3];
+    const bool ring = w == 0 || w == NW - 1;   // waves that load a row around the tile
+    const size_t rrow = (size_t)wrapm(w == 0 ? uy0 - 1 : uy0 + R, ny) * nx;
+    const unsigned ring_off = ring ? xin_off : DROP;
+    const int rslot = w == 0 ? 0 : SLOTS - 1;
+    const bool first = flags & SW_FIRST, store = flags & SW_STORE, resid = flags & SW_RESID;
+    const T *xin[3], *cin[3], *din[3];
 #pragma unroll
     for (int q = 0; q < 3; q++) {
         xin[q] = first ? a.rhs[q] : a.x_in[q];
         cin[q] = (DELTA && !first) ? a.s_in[q] : a.rhs[q];
+        din[q] = first ? a.rhs[q] : a.s_in[q];
     }
-    // prefetched level-0 plane (own columns, ring cells), carried values
-    P3<T> px[R], pc[R], pd[R], pr[RPER];
-    auto fetch = [&](int k) {
-        const size_t zo = (size_t)wrapm(k, nz) * plane;
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            px[r] = P3<T>{xin[0][zo + own[r]], xin[1][zo + own[r]], xin[2][zo + own[r]]};
-            pc[r] = P3<T>{cin[0][zo + own[r]], cin[1][zo + own[r]], cin[2][zo + own[r]]};
-            if (CHEB) {
-                if (first) pd[r] = P3<T>{T(0), T(0), T(0)};
-                else pd[r] = P3<T>{a.s_in[0][zo + own[r]], a.s_in[1][zo + own[r]], a.s_in[2][zo + own[r]]};
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < RPER; u++)
-            if (rcx[u] >= 0) pr[u] = P3<T>{xin[0][zo + roff[u]], xin[1][zo + roff[u]], xin[2][zo + roff[u]]};
+    const unsigned din_off = first ? DROP : xin_off;   // no increment yet: zero
+    auto load3 = [&](const T *const (&f)[3], size_t o, unsigned at) {
+        return P3<T>{buf_load(f[0] + o, row_bytes, at), buf_load(f[1] + o, row_bytes, at),
+                     buf_load(f[2] + o, row_bytes, at)};
+    };
+    auto publish = [&](int l, int par, int slot, const P3<T> &v) {
+        pl[l][par][slot][0][lane] = v.x;
+        pl[l][par][slot][1][lane] = v.y;
+        pl[l][par][slot][2][lane] = v.z;
     };
     // per level l (1..K) and row: partial sums of the outputs at planes p
     // (sa) and p + 1 (sb) after plane p of level l - 1 arrived, and the own
     // value (xp), carried value (cp) and increment (dp) of plane p, used when
-    // output p completes; per level l (0..K-1): carried value (oc) and
-    // increment (od) of the level's newest plane, for level l + 1
+    // output p completes; per level l (0..K-1): newest plane (val), and for
+    // l >= 1 its carried value (oc) and increment (od), for level l + 1
     const P3<T> zero3{T(0), T(0), T(0)};
-    P3<T> sa[K + 1][R], sb[K + 1][R], xp[K + 1][R], cp[K + 1][R], dp[K + 1][R], oc[K + 1][R], od[K + 1][R];
+    P3<T> val[K][R], sa[K + 1][R], sb[K + 1][R], xp[K + 1][R], cp[K + 1][R], dp[K + 1][R], oc[K + 1][R], od[K + 1][R];
+    P3<T> pe[R];   // E of the next output plane (last pass)
 #pragma unroll
-    for (int l = 0; l <= K; l++)
+    for (int r = 0; r < R; r++) {
 #pragma unroll
-        for (int r = 0; r < R; r++) sa[l][r] = sb[l][r] = xp[l][r] = cp[l][r] = dp[l][r] = oc[l][r] = od[l][r] = zero3;
-    T pe[R][3];   // E of the next output plane (last pass)
+        for (int l = 0; l < K; l++) val[l][r] = zero3;
 #pragma unroll
-    for (int r = 0; r < R; r++) pe[r][0] = pe[r][1] = pe[r][2] = T(0);
-    const bool last = flags & SW_LAST, store = flags & SW_STORE, resid = flags & SW_RESID;
+        for (int l = 0; l <= K; l++) sa[l][r] = sb[l][r] = xp[l][r] = cp[l][r] = dp[l][r] = oc[l][r] = od[l][r] = zero3;
+        pe[r] = zero3;
+    }
     double acc = 0.0;
-    const int tbeg = Z0 - K, tend = Z1 + 2 * K;
-    fetch(tbeg);
-    for (int t = tbeg; t < tend; t++) {
+    const int tbeg = Z0 - K, tend = Z1 + 2 * K, tout = Z0 + 2 * K;   // tout: level K completes plane Z0
+    // level-0 plane in flight (own rows, row around the tile): loaded a step
+    // before its use
+    P3<T> px[R], pr;
+    auto fetch = [&](int t, int zw) {
+        const size_t zin = (size_t)zw * plane;
+        const bool in = t < Z1 + K;
+#pragma unroll
+        for (int r = 0; r < R; r++) px[r] = load3(xin, zin + row[r], in ? xin_off : DROP);
+        pr = load3(xin, zin + rrow, in ? ring_off : DROP);
+    };
+    int zt = wrapm(tbeg, nz), ze = wrapm(tbeg + 1 - 2 * K, nz);   // planes t and t + 1 - 2K, wrapped
+    auto step = [&](const int t, auto out_) {
+        constexpr bool OUT = decltype(out_)::value;   // level K completes a plane of the chunk
         const int pw = (t - tbeg) & 1, prd = pw ^ 1;
 #pragma unroll
         for (int l = K; l >= 1; l--) {
             // arrival of plane p = t - 2l + 1 of level l - 1 (written at the
-            // previous step); it completes output o = p - 1 of level l
+            // previous step); it completes output o = p - 1 of level l (before
+            // the first that level l + 1 takes: a value that nothing reads)
             const int p = t - 2 * l + 1, o = p - 1;
-            if (p >= Z0 - (K - l + 1) && p < Z1 + (K - l + 1)) {
-                const bool out_ok = o >= Z0 - (K - l) && o < Z1 + (K - l);
-                P3<T> nb[R + 2][3];
-#pragma unroll
-                for (int j = 0; j < R + 2; j++)
-#pragma unroll
-                    for (int i = 0; i < 3; i++) nb[j][i] = pl[l - 1][prd][ly0 - 1 + j][tx + i];
+            if ((OUT && l == K) || (p >= Z0 - (K - l + 1) && p < Z1 + (K - l + 1))) {
+                auto edge = [&](int slot) {
+                    return P3<T>{pl[l - 1][prd][slot][0][lane], pl[l - 1][prd][slot][1][lane],
+                                 pl[l - 1][prd][slot][2][lane]};
+                };
+                const P3<T> below = edge(EDGE * w + EDGE + 1);
+                Row<T> rm = row_of<T>(edge(EDGE * w)), rc = row_of<T>(val[l - 1][0]);
 #pragma unroll
                 for (int r = 0; r < R; r++) {
-                    P3<T> win[3][3];
-#pragma unroll
-                    for (int j = 0; j < 3; j++)
-#pragma unroll
-                        for (int i = 0; i < 3; i++) win[j][i] = nb[r + j][i];
-                    const Q<T> q = inplane<T>(win);
+                    const Row<T> rp = row_of<T>(r + 1 < R ? val[l - 1][r + 1 < R ? r + 1 : r] : below);
+                    const Q<T> q = inplane<T>(rm, rc, rp);
+                    rm = rc;
+                    rc = rp;
                     P3<T> f0, f1, f2;
                     fold<T>(z, q, f0, f1, f2);
-                    if (out_ok) {
-                        const P3<T> ax = p3add(sa[l][r], f2);   // (A x) at plane o
-                        const P3<T> xo = xp[l][r], co = cp[l][r];
-                        P3<T> nv, nc = co, nd = zero3, rres = zero3;
+                    const P3<T> ax = p3add(sa[l][r], f2);   // (A x) at plane o
+                    const P3<T> xo = xp[l][r], co = cp[l][r], dd0 = dp[l][r];
+                    P3<T> nv, nc = co, nd = zero3, rres = zero3;
+#pragma unroll
+                    for (int qq = 0; qq < 3; qq++) {
+                        const T aq = comp(ax, qq);
+                        T v = DELTA ? aq : comp(co, qq) + aq;
+                        if (DELTA) setc(nc, qq, comp(co, qq) + v);
+                        if (CHEB) {
+                            const T rq = v - comp(xo, qq);
+                            const T d = fmad(a.cheb[0][0][l - 1], comp(dd0, qq), a.cheb[0][1][l - 1] * rq);
+                            setc(rres, qq, rq);
+                            setc(nd, qq, d);
+                            v = comp(xo, qq) + d;
+                        }
+                        setc(nv, qq, v);
+                    }
+                    if (l < K) {
+                        const int lw = l < K ? l : 0;
+                        oc[l][r] = nc;
+                        od[l][r] = nd;
+                        val[lw][r] = nv;
+                        if (r == 0) publish(lw, pw, EDGE * w + 1, nv);
+                        if (EDGE > 1 && r == R - 1) publish(lw, pw, EDGE * w + 2, nv);
+                    } else if (OUT) {
+                        const unsigned at = outy[r] && o < Z1 ? xout_off : DROP;
+                        const unsigned sat = store ? at : DROP;
+                        const size_t off = (size_t)o * plane + row[r];
 #pragma unroll
                         for (int qq = 0; qq < 3; qq++) {
-                            const T aq = comp(ax, qq);
-                            T v = DELTA ? aq : comp(co, qq) + aq;
-                            if (DELTA) setc(nc, qq, comp(co, qq) + v);
-                            if (CHEB) {
-                                const T rq = v - comp(xo, qq);
-                                const T d = fmad(a.cheb[0][0][l - 1], comp(dp[l][r], qq), a.cheb[0][1][l - 1] * rq);
-                                setc(rres, qq, rq);
-                                setc(nd, qq, d);
-                                v = comp(xo, qq) + d;
+                            if (LAST) {
+                                const T e = comp(pe[r], qq) + (DELTA ? comp(nc, qq) : comp(nv, qq));
+                                buf_store(a.E[qq] + off, row_bytes, at, e);
+                            } else {
+                                buf_store(a.x_out[qq] + off, row_bytes, sat, comp(nv, qq));
+                                if (DELTA) buf_store(a.s_out[qq] + off, row_bytes, sat, comp(nc, qq));
+                                if (CHEB) buf_store(a.s_out[qq] + off, row_bytes, sat, comp(nd, qq));
                             }
-                            setc(nv, qq, v);
                         }
-                        if (l < K) {
-                            oc[l][r] = nc;
-                            od[l][r] = nd;
-                            pl[l][pw][ly0 + r][tx + 1] = nv;
-                        } else if (outc[r] && o >= Z0 && o < Z1) {
-                            const size_t off = (size_t)o * plane + own[r];
+                        if (resid) {
+                            double s = 0.0;
 #pragma unroll
                             for (int qq = 0; qq < 3; qq++) {
-                                if (resid) {
-                                    const double dd = CHEB    ? (double)comp(rres, qq)
-                                                      : DELTA ? (double)comp(nv, qq)
-                                                              : (double)comp(nv, qq) - (double)comp(xo, qq);
-                                    acc += dd * dd;
-                                }
-                                if (store) {
-                                    a.x_out[qq][off] = comp(nv, qq);
-                                    if (DELTA) a.s_out[qq][off] = comp(nc, qq);
-                                    if (CHEB) a.s_out[qq][off] = comp(nd, qq);
-                                }
-                                if (last) a.E[qq][off] = pe[r][qq] + (DELTA ? comp(nc, qq) : comp(nv, qq));
+                                const double dd = CHEB    ? (double)comp(rres, qq)
+                                                  : DELTA ? (double)comp(nv, qq)
+                                                          : (double)comp(nv, qq) - (double)comp(xo, qq);
+                                s += dd * dd;
                             }
+                            acc += at != DROP ? s : 0.0;
                         }
                     }
                     sa[l][r] = p3add(sb[l][r], f1);
                     sb[l][r] = f0;
-                    xp[l][r] = P3<T>{q.X, q.Y, q.Z};
-                    cp[l][r] = oc[l - 1][r];
-                    if (CHEB) dp[l][r] = od[l - 1][r];
+                    if (CHEB || l == K) xp[l][r] = P3<T>{q.X, q.Y, q.Z};
+                    if (l > 1) {
+                        cp[l][r] = oc[l - 1][r];
+                        if (CHEB) dp[l][r] = od[l - 1][r];
+                    }
                 }
             }
         }
-        // level 0: plane t (own columns and ring)
-        if (t < Z1 + K) {
+        // carried values of the plane that level 1 completes at the next step
+        const size_t zc = (size_t)(zt == 0 ? nz - 1 : zt - 1) * plane;
+        const bool need = t - 1 > Z0 - K && t - 1 < Z1 + K - 1;
 #pragma unroll
-            for (int r = 0; r < R; r++) {
-                oc[0][r] = pc[r];
-                od[0][r] = pd[r];
-                pl[0][pw][ly0 + r][tx + 1] = px[r];
-            }
-#pragma unroll
-            for (int u = 0; u < RPER; u++)
-                if (rcx[u] >= 0) pl[0][pw][rcy[u]][rcx[u]] = pr[u];
-            if (t + 1 < Z1 + K) fetch(t + 1);
+        for (int r = 0; r < R; r++) {
+            cp[1][r] = load3(cin, zc + row[r], need ? xin_off : DROP);
+            if (CHEB) dp[1][r] = load3(din, zc + row[r], need ? din_off : DROP);
         }
-        // E of the output plane of the next step
-        if (last) {
-            const int on = t + 1 - 2 * K;
-            if (on >= Z0 && on < Z1)
+        if (LAST) {   // E of the plane that level K completes at the next step
 #pragma unroll
-                for (int r = 0; r < R; r++)
-                    if (outc[r])
-#pragma unroll
-                        for (int qq = 0; qq < 3; qq++) pe[r][qq] = a.E[qq][(size_t)on * plane + own[r]];
+            for (int r = 0; r < R; r++)
+                pe[r] = load3(a.E, (size_t)ze * plane + row[r], t + 1 >= tout && t + 1 < tend ? xout_off : DROP);
         }
+#pragma unroll
+        for (int r = 0; r < R; r++) val[0][r] = px[r];
+        publish(0, pw, EDGE * w + 1, px[0]);
+        if (EDGE > 1) publish(0, pw, EDGE * w + 2, px[R - 1]);
+        if (ring) publish(0, pw, rslot, pr);
+        zt = zt + 1 == nz ? 0 : zt + 1;
+        fetch(t + 1, zt);
+        ze = ze + 1 == nz ? 0 : ze + 1;
         lds_barrier();
+    };
+    fetch(tbeg, zt);
+    int t = tbeg;
+    for (; t < tout; t++) step(t, std::false_type{});
+    // pairs of steps let the values carried from plane to plane change their
+    // registers instead of being moved (512^3 FP32: 7.5 against 7.7 ms per
+    // step); the delta form, which stores twice as much, is faster without
+    // (33.4 against 35.9)
+    if constexpr (DELTA) {
+        for (; t < tend; t++) step(t, std::true_type{});
+    } else {
+        for (; t < tend; t += 2) {
+            step(t, std::true_type{});
+            step(t + 1, std::true_type{});
+        }
     }
     if (resid) {
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        const int lane = tid & 63, wv = tid >> 6;
         __syncthreads();
-        if (lane == 0) sred[wv] = acc;
+        if (lane == 0) sred[w] = acc;
         __syncthreads();
-        if (tid == 0) {
+        if (threadIdx.x == 0) {
             double s_ = 0.0;
-            for (int q = 0; q < NTH / 64; q++) s_ += sred[q];
+            for (int q = 0; q < NW; q++) s_ += sred[q];
             a.partial[2 * lin] = s_;
             a.partial[2 * lin + 1] = 0.0;
         }
@@ -358,74 +433,96 @@ Zc<T> zcoef(const Coef<T> &c)
     return z;
 }
 
-// Number of z chunks of a launch with ncol column tiles: every workgroup
-// marches Lz + 3K plane steps (its chunk and the pipeline's fill and
-// drain), and the workgroups run in rounds of `slots` (the co-resident
-// limit), so the pass takes about ceil(ncol nzc / slots) (Lz + 3K) plane
-// steps; the count minimising that is taken (chunks of at least 8K planes).
-inline int z_chunks(int ncol, int nz, int K, int slots)
+// A launch's z chunks and its time in the model that sizes it: a workgroup
+// marches Lz + 3K plane steps (its chunk and the pipeline's fill and drain),
+// the workgroups run in rounds of one per CU, and a step costs its rows plus
+// about 8 (the barrier and the latencies of a step on a CU that is not full;
+// fitted on 64^3 to 512^3).  Chunks of two planes pay on small grids, where
+// they are what fills the CUs.
+struct Split {
+    int gx, gy, Lz, nzc;
+    double cost;
+};
+
+template <int K, int R, int NW>
+Split split(int nx, int ny, int nz, int cus)
 {
-    const int maxc = std::max(1, nz / (8 * K));
-    int best = 1;
-    double bt = 1e300;
-    for (int n = 1; n <= maxc; n++) {
-        const int Lz = (nz + n - 1) / n, nc = (nz + Lz - 1) / Lz;
-        const double rounds = slots > 0 ? (double)(((int64_t)ncol * nc + slots - 1) / slots) : (double)ncol * nc;
-        const double t = rounds * (Lz + 3 * K);
-        if (t < bt * (1.0 - 1e-9)) { bt = t; best = nc; }
+    constexpr int OX = 64 - 2 * K, OY = NW * R - 2 * (K - 1);
+    Split best{(nx + OX - 1) / OX, (ny + OY - 1) / OY, nz, 1, 1e300};
+    const int64_t ncol = (int64_t)best.gx * best.gy;
+    for (int n = 1; n <= std::max(1, nz / 2); n++) {
+        const int Lz = (nz + n - 1) / n, nzc = (nz + Lz - 1) / Lz;
+        const double cost = (double)((ncol * nzc + cus - 1) / cus) * (Lz + 3 * K) * (NW * R + 8);
+        if (cost < best.cost * (1.0 - 1e-9)) best.cost = cost, best.Lz = Lz, best.nzc = nzc;
     }
     return best;
 }
 
-template <typename T, int K, int FORM, int TX, int TYT, int R>
-hipError_t launch_k(const Coef<T> &c, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+inline int cu_count()
 {
-    constexpr int OX = TX - 2 * (K - 1), OY = TYT * R - 2 * (K - 1);
-    // the partial-sum buffer holds a slot per 64 x 4 cells of each plane
-    static_assert(OX * OY >= 256, "tile too small for the partial-sum buffer");
-    const auto kern = k3_stream<T, K, FORM, TX, TYT, R>;
-    static std::atomic<int> slot_cache[MX_MAX_DEVICES];
-    const int slots = per_device(slot_cache, [&]() {
-        int dev = 0, cu = 0, per = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void *)kern, TX * TYT, 0) != hipSuccess) return 0;
-        return per * cu;
+    static std::atomic<int> cache[MX_MAX_DEVICES];
+    return per_device(cache, [] {
+        int dev = 0, cu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1)
+            return 256;
+        return cu;
     });
-    const int gx = (c.nx + OX - 1) / OX, gy = (c.ny + OY - 1) / OY;
-    const int nzc = z_chunks(gx * gy, c.nz, K, slots);
-    const int Lz = (c.nz + nzc - 1) / nzc;
-    dim3 g(gx, gy, nzc);
+}
+
+template <typename T, int K, int FORM, bool LAST, int R, int NW>
+hipError_t launch_k(const Coef<T> &c, const Split &p, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+{
+    dim3 g(p.gx, p.gy, p.nzc);
     *nwg = g.x * g.y * g.z;
-    hipLaunchKernelGGL(kern, g, dim3(TX * TYT), 0, s, c, zcoef(c), a, flags, Lz);
+    hipLaunchKernelGGL((k3_stream<T, K, FORM, LAST, R, NW>), g, dim3(64 * NW), 0, s, c, zcoef(c), a, flags, p.Lz);
     return hipGetLastError();
 }
 
-// FP32 passes of two and three sweeps: 64 x 16 columns, one per thread
-// (1024 threads; a tile's input rows touch about 3 cache lines for 60 output
-// columns instead of 2 for 28): 512^3, three sweeps per pass, 2.11 against
-// 2.33 ms per delta-form pass and 2.56 against 3.07 per Chebyshev pass; 64 x
-// 8 threads with two rows each measured as 32 x 16.  FP64 passes of two
-// sweeps: 64 x 16 columns on 64 x 8 threads with two rows each (a 64 x 16
-// FP64 tile of 1024 threads spills), 3.49 against 4.00 ms per delta-form
-// pass at 512^3; the FP64 Chebyshev form spills there and keeps 32 x 16.
-// Single sweeps: 32 x 16 (two rows per thread on a 32 x 8 thread block
-// measured the same at three sweeps per pass, 32 x 32 columns slower).
-template <typename T, int FORM>
-hipError_t launch_form(const Coef<T> &c, int k, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+// Tiles.  Alg 1 and the delta form: two rows per wave (three or four halve the
+// waves of a CU or spill: 512^3 FP32, ms per step of ten sweeps: 7.5 with 12
+// waves of two rows, 8.1 with 16 of one, 8.2 with 8 of three, 8.5 with 8 of
+// four), FP32 on 12 or 8 waves, FP64 on 8 or 4: the smaller one where its finer
+// cut of the grid outweighs its larger rim (48 x 40 x 32 FP64: 126 against
+// 153 us per step; 160 x 144 x 128 FP32: 496 against 514; 256^3 FP64 the other
+// way, 4.01 against 3.84 ms).  The Chebyshev form carries half as much again
+// per point and has one row per wave (512^3 FP32: 20.0 ms per step with 16
+// waves, 23.6 with 8 of two rows; 160 x 144 x 128 FP64: 2.08 with 12 waves,
+// 2.74 with 8 of two rows).
+template <typename T, int K, int FORM, bool LAST>
+hipError_t launch_shape(const Coef<T> &c, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
 {
     constexpr bool F32 = sizeof(T) == 4;
+    if constexpr (FORM == FM_CHEB) {
+        constexpr int NW = F32 ? 16 : 12;
+        return launch_k<T, K, FORM, LAST, 1, NW>(c, split<K, 1, NW>(c.nx, c.ny, c.nz, cu_count()), flags, a, s, nwg);
+    } else {
+        constexpr int NL = F32 ? 12 : 8, NS = F32 ? 8 : 4;
+        const Split l = split<K, 2, NL>(c.nx, c.ny, c.nz, cu_count());
+        const Split m = split<K, 2, NS>(c.nx, c.ny, c.nz, cu_count());
+        if (m.cost < l.cost) return launch_k<T, K, FORM, LAST, 2, NS>(c, m, flags, a, s, nwg);
+        return launch_k<T, K, FORM, LAST, 2, NL>(c, l, flags, a, s, nwg);
+    }
+}
+
+template <typename T, int FORM, bool LAST>
+hipError_t launch_form(const Coef<T> &c, int k, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+{
     switch (k) {
-    case 1: return launch_k<T, 1, FORM, 32, 16, 1>(c, flags, a, s, nwg);
-    case 2:
-        if constexpr (F32) return launch_k<T, 2, FORM, 64, 16, 1>(c, flags, a, s, nwg);
-        else if constexpr (FORM != FM_CHEB) return launch_k<T, 2, FORM, 64, 8, 2>(c, flags, a, s, nwg);
-        else return launch_k<T, 2, FORM, 32, 16, 1>(c, flags, a, s, nwg);
+    case 1: return launch_shape<T, 1, FORM, LAST>(c, flags, a, s, nwg);
+    case 2: return launch_shape<T, 2, FORM, LAST>(c, flags, a, s, nwg);
     case 3:
-        if constexpr (F32) return launch_k<T, 3, FORM, 64, 16, 1>(c, flags, a, s, nwg);
+        if constexpr (sizeof(T) == 4) return launch_shape<T, 3, FORM, LAST>(c, flags, a, s, nwg);
         return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
+}
+
+template <typename T, int FORM>
+hipError_t launch_last(const Coef<T> &c, int k, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+{
+    if (flags & SW_LAST) return launch_form<T, FORM, true>(c, k, flags, a, s, nwg);
+    return launch_form<T, FORM, false>(c, k, flags, a, s, nwg);
 }
 
 }  // namespace
@@ -437,9 +534,9 @@ hipError_t launch_stream3d(const Coef<T> &c, int k, int form, int flags, const S
                            int *nwg)
 {
     if (k < 1 || k > stream3d_kmax(sizeof(T) == 8)) return hipErrorInvalidValue;
-    if (form == FM_CHEB) return launch_form<T, FM_CHEB>(c, k, flags, a, s, nwg);
-    if (form == FM_DELTA) return launch_form<T, FM_DELTA>(c, k, flags, a, s, nwg);
-    return launch_form<T, FM_STD>(c, k, flags, a, s, nwg);
+    if (form == FM_CHEB) return launch_last<T, FM_CHEB>(c, k, flags, a, s, nwg);
+    if (form == FM_DELTA) return launch_last<T, FM_DELTA>(c, k, flags, a, s, nwg);
+    return launch_last<T, FM_STD>(c, k, flags, a, s, nwg);
 }
 
 template hipError_t launch_stream3d<float>(const Coef<float> &, int, int, int, const SweepArgs<float> &, hipStream_t,

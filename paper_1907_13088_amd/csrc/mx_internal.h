@@ -114,6 +114,33 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// One value of an array of `bytes` bytes, `at` bytes from its start.  From
+// BUF_DROP, as from any offset past the end, a load gives zero and a store is
+// dropped (bounds check of raw buffers), so lanes without work need no branch
+// around their memory operations.
+constexpr unsigned BUF_DROP = 0xffffffffu;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float buf_load(const float *p, unsigned bytes, unsigned at)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(buf_rsrc(p, bytes), (int)at, 0, 0));
+}
+__device__ __forceinline__ double buf_load(const double *p, unsigned bytes, unsigned at)
+{
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(buf_rsrc(p, bytes), (int)at, 0, 0));
+}
+__device__ __forceinline__ void buf_store(float *p, unsigned bytes, unsigned at, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), buf_rsrc(p, bytes), (int)at, 0, 0);
+}
+__device__ __forceinline__ void buf_store(double *p, unsigned bytes, unsigned at, double v)
+{
+    using U2 = unsigned __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), buf_rsrc(p, bytes), (int)at, 0, 0);
+}
+
 // Work item of workgroup b (linear index) in a launch of n workgroups, such
 // that each XCD receives one contiguous range of items.  Workgroups are dealt
 // round-robin over the 8 XCDs (workgroup b runs on XCD b % 8), so XCD x holds
@@ -388,6 +415,7 @@ hipError_t launch_pic_charge(int64_t np, int nx, int ny, T dx, T dy, T cq, const
 // filter passes of the current, dE' (and its FP64 partial norms when
 // a.partial is set); *nwg receives the workgroup count
 int front3d_max_passes();
+bool front3d_fits(int64_t nx, int64_t ny, size_t elem);   // a plane is under 4 GiB
 template <typename T>
 hipError_t launch_front3d(const Coef<T> &c, int filter_passes, const FrontArgs<T> &a, const T *const Bin[3],
                           hipStream_t s, int *nwg);
