@@ -13,7 +13,8 @@
 // curl of Lambda B needs no neighbour's result: the halo is recomputed), and
 // dE' at plane t - 2 from the three newest B^{n+1/2} planes.  The current is
 // filtered along x and y in LDS and along z by p cascaded three-tap passes in
-// registers, each thread for its own column.  Two barriers per plane.
+// registers, each thread for its own column.  Two barriers per plane, which
+// wait for LDS alone: loads and stores stay in flight across them.
 #include <algorithm>
 
 #include "mx_internal.h"
@@ -108,25 +109,36 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
     const bool has_j = a.J0[0] != nullptr;
     const T *Bin[3] = {Bx_in, By_in, Bz_in};
 
-    // tile cells of this thread, fixed for the whole march
+    // tile cells of this thread, fixed for the whole march: byte offsets in a
+    // plane, past its end where there is no cell (a plane is under 4 GiB).
+    // ALL (FP64): no branch stands around a load, store or cell, so the number
+    // of operations in flight is known and a wait for the oldest planes
+    // leaves the newer ones alone (256^3: 0.52 against 0.62 ms).  FP32 has two
+    // planes in flight and skips the cells it does not have (512^3: 1.84
+    // against 2.2 ms).
+    constexpr bool ALL = sizeof(T) == 8;
+    const unsigned bytes = (unsigned)(plane * sizeof(T));
+    auto cell = [&](int x, int y) {
+        return ((unsigned)wrapm(y, ny) * (unsigned)nx + (unsigned)wrapm(x, nx)) * (unsigned)sizeof(T);
+    };
     unsigned eoff[EPER];
     int eidx[EPER];
     for (int u = 0; u < EPER; u++) {
         const int idx = tid + u * FT;
         eidx[u] = idx < ECELLS ? idx : -1;
         const int ix = idx % EX, iy = idx / EX;
-        eoff[u] = (unsigned)wrapm(Y0 - 1 + iy, ny) * (unsigned)nx + wrapm(X0 - 1 + ix, nx);
+        eoff[u] = idx < ECELLS ? cell(X0 - 1 + ix, Y0 - 1 + iy) : BUF_DROP;
     }
     unsigned boff[BPER];
     int bidx[BPER];
-    bool bown[BPER];
+    unsigned bst[BPER];   // of the owned cells
     for (int u = 0; u < BPER; u++) {
         const int idx = tid + u * FT;
         bidx[u] = idx < BCELLS ? idx : -1;
         const int ix = idx % BX, iy = idx / BX;
         const int gx = X0 - 1 + ix, gy = Y0 - 1 + iy;
-        boff[u] = (unsigned)wrapm(gy, ny) * (unsigned)nx + wrapm(gx, nx);
-        bown[u] = bidx[u] >= 0 && ix >= 1 && ix <= FX && iy >= 1 && iy <= FY && gx < nx && gy < ny;
+        boff[u] = idx < BCELLS ? cell(gx, gy) : BUF_DROP;
+        bst[u] = ix >= 1 && ix <= FX && iy >= 1 && iy <= FY && gx < nx && gy < ny ? boff[u] : BUF_DROP;
     }
     unsigned joff[JT::PER];
     int jidx[JT::PER];
@@ -134,35 +146,38 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
         const int idx = tid + u * FT;
         jidx[u] = (has_j && idx < JT::CELLS) ? idx : -1;
         const int ix = idx % JT::JX, iy = idx / JT::JX;
-        joff[u] = (unsigned)wrapm(Y0 - P + iy, ny) * (unsigned)nx + wrapm(X0 - P + ix, nx);
+        joff[u] = jidx[u] >= 0 ? cell(X0 - P + ix, Y0 - P + iy) : BUF_DROP;
     }
     const bool out = X0 + tx < nx && Y0 + ty < ny;
-    const unsigned own = out ? (unsigned)(Y0 + ty) * (unsigned)nx + (unsigned)(X0 + tx) : 0u;
+    const unsigned own = out ? cell(X0 + tx, Y0 + ty) : BUF_DROP;
 
     // prefetched planes (registers): a ring of PF sets, set (t - t0) % PF
     // holds what march step t stages
     constexpr int PF = G::PF;
     T eP[PF][EPER][3], bP[PF][BPER][3], jP[PF][JT::PER][3];
-    auto fetchE = [&](int k, auto st) {
+    auto fetchE = [&](int k, bool in, auto st) {
+        if (!ALL && !in) return;
         constexpr int S = decltype(st)::value;
         const size_t zo = (size_t)wrapm(k, nz) * plane;
         for (int u = 0; u < EPER; u++)
-            if (eidx[u] >= 0)
-                for (int q = 0; q < 3; q++) eP[S][u][q] = a.E[q][zo + eoff[u]];
+            if (ALL || eidx[u] >= 0)
+                for (int q = 0; q < 3; q++) eP[S][u][q] = buf_load(a.E[q] + zo, in ? bytes : 0u, eoff[u]);
     };
-    auto fetchB = [&](int k, auto st) {
+    auto fetchB = [&](int k, bool in, auto st) {
+        if (!ALL && !in) return;
         constexpr int S = decltype(st)::value;
         const size_t zo = (size_t)wrapm(k, nz) * plane;
         for (int u = 0; u < BPER; u++)
-            if (bidx[u] >= 0)
-                for (int q = 0; q < 3; q++) bP[S][u][q] = Bin[q][zo + boff[u]];
+            if (ALL || bidx[u] >= 0)
+                for (int q = 0; q < 3; q++) bP[S][u][q] = buf_load(Bin[q] + zo, in ? bytes : 0u, boff[u]);
     };
-    auto fetchJ = [&](int k, auto st) {
+    auto fetchJ = [&](int k, bool in, auto st) {
+        if (!ALL && !in) return;
         constexpr int S = decltype(st)::value;
         const size_t zo = (size_t)wrapm(k, nz) * plane;
         for (int u = 0; u < JT::PER; u++)
-            if (jidx[u] >= 0)
-                for (int q = 0; q < 3; q++) jP[S][u][q] = a.J0[q][zo + joff[u]];
+            if (ALL || jidx[u] >= 0)
+                for (int q = 0; q < 3; q++) jP[S][u][q] = buf_load(a.J0[q] + zo, in ? bytes : 0u, joff[u]);
     };
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, PF - 1>;
@@ -178,13 +193,13 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
     // t0 fills the z filter (2P steps) and the B^{n+1/2} planes below Z0.
     const int t0 = min(Z0 - 1, Z0 + 2 - 2 * P);
     double acc = 0.0;
-    fetchE(t0, S0{});
-    fetchB(t0 - 1, S0{});
-    if (has_j) fetchJ(t0 - 2 + P, S0{});
+    fetchE(t0, true, S0{});
+    fetchJ(t0 - 2 + P, has_j, S0{});
+    fetchB(t0 - 1, true, S0{});
     if constexpr (PF == 2) {
-        fetchE(t0 + 1, S1{});
-        fetchB(t0, S1{});
-        if (has_j) fetchJ(t0 - 1 + P, S1{});
+        fetchE(t0 + 1, true, S1{});
+        fetchJ(t0 - 1 + P, has_j, S1{});
+        fetchB(t0, true, S1{});
     }
     auto body = [&](const int t, auto st) {
         constexpr int S = decltype(st)::value;
@@ -207,38 +222,37 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
             if constexpr (PF == 1) return bold[u][q];
             else return bP[S][u][q];
         };
-        __syncthreads();
+        lds_barrier();
         // the planes of march step t + PF into the set just staged
-        if (t + PF <= Z1 + 1) {
-            fetchE(t + PF, st);
-            if (has_j) fetchJ(t - 2 + P + PF, st);
-        }
-        if constexpr (PF == 1) fetchB(t, st);
+        const bool more = t + PF <= Z1 + 1;
+        fetchE(t + PF, more, st);
+        fetchJ(t - 2 + P + PF, has_j && more, st);
+        if constexpr (PF == 1) fetchB(t, more, st);
         // --- B^{n+1/2} at plane t - 1 on the tile and its one-cell halo
         const int kb = t - 1;
         const int sb = (kb - t0 + 3) % 3;
-        if (t > t0) {
-            for (int u = 0; u < BPER; u++) {
-                if (bidx[u] < 0) continue;
-                const int ix = bidx[u] % BX, iy = bidx[u] / BX;   // E tile (ix, iy) is the same cell
-                auto E0 = [&](int q, int dx, int dy) { return sE[sep][q][iy + dy][ix + dx]; };
-                auto E1 = [&](int q) { return sE[se][q][iy][ix]; };   // plane kb + 1
-                const T ex = E0(0, 0, 0), ey = E0(1, 0, 0), ez = E0(2, 0, 0);
-                const T bx = bget(u, 0) - (c.tdy * (E0(2, 0, 1) - ez) - c.tdz * (E1(1) - ey));
-                const T by = bget(u, 1) - (c.tdz * (E1(0) - ex) - c.tdx * (E0(2, 1, 0) - ez));
-                const T bz = bget(u, 2) - (c.tdx * (E0(1, 1, 0) - ey) - c.tdy * (E0(0, 0, 1) - ex));
+        for (int u = 0; u < BPER; u++) {
+            if (!ALL && (bidx[u] < 0 || t == t0)) continue;
+            const int idx = bidx[u] < 0 ? 0 : bidx[u];
+            const int ix = idx % BX, iy = idx / BX;   // E tile (ix, iy) is the same cell
+            auto E0 = [&](int q, int dx, int dy) { return sE[sep][q][iy + dy][ix + dx]; };
+            auto E1 = [&](int q) { return sE[se][q][iy][ix]; };   // plane kb + 1
+            const T ex = E0(0, 0, 0), ey = E0(1, 0, 0), ez = E0(2, 0, 0);
+            const T bx = bget(u, 0) - (c.tdy * (E0(2, 0, 1) - ez) - c.tdz * (E1(1) - ey));
+            const T by = bget(u, 1) - (c.tdz * (E1(0) - ex) - c.tdx * (E0(2, 1, 0) - ez));
+            const T bz = bget(u, 2) - (c.tdx * (E0(1, 1, 0) - ey) - c.tdy * (E0(0, 0, 1) - ex));
+            if (bidx[u] >= 0) {
                 sB[sb][0][iy][ix] = bx;
                 sB[sb][1][iy][ix] = by;
                 sB[sb][2][iy][ix] = bz;
-                if (bown[u] && kb >= Z0 && kb < Z1) {
-                    const size_t o = (size_t)kb * plane + boff[u];
-                    a.B[0][o] = bx;
-                    a.B[1][o] = by;
-                    a.B[2][o] = bz;
-                }
             }
+            const unsigned at = kb >= Z0 && kb < Z1 ? bst[u] : BUF_DROP;
+            const size_t zo = (size_t)kb * plane;
+            buf_store(a.B[0] + zo, bytes, at, bx);
+            buf_store(a.B[1] + zo, bytes, at, by);
+            buf_store(a.B[2] + zo, bytes, at, bz);
         }
-        if constexpr (PF == 2) fetchB(t + 1, st);
+        if constexpr (PF == 2) fetchB(t + 1, more, st);
         // --- x filter of the staged current plane
         if (has_j) {
             for (int u = 0; u < JT::XPER; u++) {
@@ -252,7 +266,7 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
         // --- y filter, then the z filter: the filtered current at plane t - 2
         T jf[3] = {T(0), T(0), T(0)};
         if (has_j) {
@@ -279,7 +293,7 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
         }
         // --- dE' at plane t - 2 (own cell; B^{n+1/2} planes t - 3 .. t - 1)
         const int kd = t - 2;
-        if (out && kd >= Z0 && kd < Z1) {
+        if (ALL || (out && kd >= Z0 && kd < Z1)) {
             const int s0 = (kd - t0 + 3) % 3, sm = (kd - 1 - t0 + 3) % 3, sp = (kd + 1 - t0 + 3) % 3;
             const int L = c.lumped;
             const int cx = tx + 1, cy = ty + 1;
@@ -299,11 +313,13 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
             const T vx = c.tdy * (azbz - azBz(0, -1)) - c.tdz * (ayby - ayBy(0, -1)) - a.env_src * jf[0];
             const T vy = c.tdz * (axbx - axBx(0, -1)) - c.tdx * (azbz - azBz(-1, 0)) - a.env_src * jf[1];
             const T vz = c.tdx * (ayby - ayBy(-1, 0)) - c.tdy * (axbx - axBx(-1, 0)) - a.env_src * jf[2];
-            const size_t o = (size_t)kd * plane + own;
-            a.dEp[0][o] = vx;
-            a.dEp[1][o] = vy;
-            a.dEp[2][o] = vz;
-            acc += (double)vx * vx + (double)vy * vy + (double)vz * vz;
+            const size_t zo = (size_t)kd * plane;
+            const unsigned at = kd >= Z0 && kd < Z1 ? own : BUF_DROP;
+            buf_store(a.dEp[0] + zo, bytes, at, vx);
+            buf_store(a.dEp[1] + zo, bytes, at, vy);
+            buf_store(a.dEp[2] + zo, bytes, at, vz);
+            const double v2 = (double)vx * vx + (double)vy * vy + (double)vz * vz;
+            acc += at == BUF_DROP ? 0.0 : v2;
         }
     };
     int t = t0;
@@ -332,6 +348,8 @@ __global__ __launch_bounds__(Geo<T>::FT) void k3_front(Coef<T> c, FrontArgs<T> a
 
 int front3d_max_passes() { return 2; }
 
+bool front3d_fits(int64_t nx, int64_t ny, size_t elem) { return nx * ny * (int64_t)elem <= 0xffffffffll; }
+
 template <typename T>
 hipError_t launch_front3d(const Coef<T> &c, int filter_passes, const FrontArgs<T> &a, const T *const Bin[3],
                           hipStream_t s, int *nwg)
@@ -341,7 +359,13 @@ hipError_t launch_front3d(const Coef<T> &c, int filter_passes, const FrontArgs<T
     using G = Geo<T>;
     const void *k = p == 0 ? (const void *)k3_front<T, 0> : p == 1 ? (const void *)k3_front<T, 1>
                                                                    : (const void *)k3_front<T, 2>;
-    // z chunks: one round of the resident workgroups, each chunk at least 16 planes
+    // z chunks: every workgroup marches its chunk and the steps that fill the
+    // z filter and the B planes below it, in rounds of the resident
+    // workgroups; the count with the fewest plane steps is taken.  Chunks as
+    // short as two planes fill the CUs on small grids (48 x 40 x 32 FP64, whole
+    // step: 86 us against 126 with chunks of 16 planes or more), and a second
+    // round that holds a few workgroups is avoided (160 x 144 x 128 FP64: 216
+    // workgroups of 36 steps, 153 us, against 270 of 30 in two rounds, 225)
     static std::atomic<int> resident[3][MX_MAX_DEVICES];
     const int slots = per_device(resident[p], [k] {
         int o = 0, dev = 0, cu = 0;
@@ -351,9 +375,13 @@ hipError_t launch_front3d(const Coef<T> &c, int filter_passes, const FrontArgs<T
         return o * cu;
     });
     const int gx = (c.nx + G::FX - 1) / G::FX, gy = (c.ny + G::FY - 1) / G::FY;
-    int nzc = std::max(1, std::min(c.nz / 16, (slots + gx * gy - 1) / (gx * gy)));
-    const int Lz = (c.nz + nzc - 1) / nzc;
-    nzc = (c.nz + Lz - 1) / Lz;
+    int nzc = 1, Lz = c.nz;
+    double best = 1e300;
+    for (int n = 1; n <= std::max(1, c.nz / 2); n++) {
+        const int L = (c.nz + n - 1) / n, m = (c.nz + L - 1) / L;
+        const double steps = (double)(((int64_t)gx * gy * m + slots - 1) / slots) * (L + 2 + std::max(1, 2 * p - 2));
+        if (steps < best * (1.0 - 1e-9)) best = steps, nzc = m, Lz = L;
+    }
     dim3 g(gx, gy, nzc);
     *nwg = g.x * g.y * g.z;
     if (p == 0) hipLaunchKernelGGL((k3_front<T, 0>), g, dim3(G::FT), 0, s, c, a, Bin[0], Bin[1], Bin[2], Lz);

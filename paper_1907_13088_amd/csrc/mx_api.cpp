@@ -1397,7 +1397,7 @@ int step_impl(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
             // B components of active blocks now live in the other buffer
             if (c.blocks & 1) g->bloc[2] ^= 1;
             if (c.blocks & 2) { g->bloc[0] ^= 1; g->bloc[1] ^= 1; }
-        } else if (c.filter_passes <= front3d_max_passes()) {
+        } else if (c.filter_passes <= front3d_max_passes() && front3d_fits(c.n[0], c.n[1], sizeof(T))) {
             // one pass: Faraday into the other B buffer, filter, dE'
             const T *Bin[3];
             FrontArgs<T> a{};
