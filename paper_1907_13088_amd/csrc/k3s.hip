@@ -99,26 +99,6 @@ __device__ __forceinline__ T avg6(T fm, T f0, T fp)
     return fmad(d2(fm, f0, fp), T(1.0 / 6.0), f0);
 }
 
-// value of the lane one column to the left or right (zero at the tile's edge,
-// in columns that no output needs)
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v)
-{
-    const long long u = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-template <typename T>
-__device__ __forceinline__ T from_left(T v) { return dpp<0x138>(v); }    // wave_shr:1, lane - 1
-template <typename T>
-__device__ __forceinline__ T from_right(T v) { return dpp<0x130>(v); }   // wave_shl:1, lane + 1
-
 // one row of a plane: its values and the differences along x that the rows
 // above and below it use too
 template <typename T>

@@ -46,11 +46,12 @@ __device__ __forceinline__ T avg(T fm, T f0, T fp, int lumped)
 //   y: tdz (vx[k+1] - vx) - tdx (vz[i+1] - vz)
 //   z: tdx (vy[i+1] - vy) - tdy (vx[j+1] - vx)
 // and, when acc is set, acc += sc v on the stepped components (the current
-// gradient's accumulator, the same axpy as k_axpy, while v is at hand)
+// gradient's accumulator, the same axpy as k_axpy, while v is at hand; acc =
+// 0 + sc v where `fresh`, which spares clearing and reading it)
 template <typename T>
 __global__ __launch_bounds__(NT) void k_adj_curlB(Coef<T> c, int ndim, int blocks, const T *vx,
                                                   const T *vy, const T *vz, T *Bx, T *By, T *Bz, T sc, T *ax,
-                                                  T *ay, T *az)
+                                                  T *ay, T *az, bool fresh)
 {
     Ix id{c.nx, c.ny, c.nz, 0, 0, 0};
     if (!cell(c.nx, c.ny, id)) return;
@@ -78,11 +79,12 @@ __global__ __launch_bounds__(NT) void k_adj_curlB(Coef<T> c, int ndim, int block
     }
     if (te) Bz[o] += d3 ? avg(kz(0, 0, -1), kz(0, 0, 0), kz(0, 0, 1), L) : kz(0, 0, 0);
     if (ax) {
+        auto add = [&](T *acc, const T *v) { acc[o] = (fresh ? T(0) : acc[o]) + sc * v[o]; };
         if (te) {
-            ax[o] += sc * vx[o];
-            ay[o] += sc * vy[o];
+            add(ax, vx);
+            add(ay, vy);
         }
-        if (tm) az[o] += sc * vz[o];
+        if (tm) add(az, vz);
     }
 }
 
@@ -117,6 +119,48 @@ __global__ __launch_bounds__(NT) void k_filter_axis(Coef<T> c, int axis, const T
     const int di = axis == 0, dj = axis == 1, dk = axis == 2;
     dst[id.at(0, 0, 0)] = T(0.25) * src[id.at(-di, -dj, -dk)] + T(0.5) * src[id.at(0, 0, 0)]
                         + T(0.25) * src[id.at(di, dj, dk)];
+}
+
+// dst += scale F src on one 2D component per blockIdx.z: P passes over x and
+// y in turn.  A wave holds 64 columns by FTY + 2P rows in registers (x
+// neighbours from the neighbouring lanes), writes the inner 64 - 2P by FTY:
+// no LDS and no barrier.  Bound by HBM: src and dst once each way, where P
+// passes per axis by k_filter_axis and k_axpy move the plane 4P + 3 times
+// (2048^2 FP32, P = 3, three components: 51 us here, 66 us with the tile in
+// LDS, 234 us by 18 + 3 launches).  The same expressions in the same order.
+constexpr int FTY = 24;
+template <typename T, int P>
+__global__ __launch_bounds__(NT) void k_filter2_add(int nx, int ny, T scale, const T *s0, const T *s1, const T *s2,
+                                                    T *d0, T *d1, T *d2)
+{
+    constexpr int H = FTY + 2 * P;
+    const T *src = blockIdx.z == 0 ? s0 : (blockIdx.z == 1 ? s1 : s2);
+    T *dst = blockIdx.z == 0 ? d0 : (blockIdx.z == 1 ? d1 : d2);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = blockIdx.x * (64 - 2 * P) - P + lane, Y0 = (blockIdx.y * (NT / 64) + w) * FTY;
+    if (Y0 >= ny) return;
+    auto wrap = [](int i, int n) { i %= n; return i < 0 ? i + n : i; };
+    const int xw = wrap(x, nx);
+    T v[H];
+#pragma unroll
+    for (int j = 0; j < H; j++) v[j] = (src + (size_t)wrap(Y0 - P + j, ny) * nx)[xw];
+#pragma unroll
+    for (int r = 1; r <= P; r++) {
+#pragma unroll
+        for (int j = r - 1; j < H - (r - 1); j++)
+            v[j] = T(0.25) * from_left(v[j]) + T(0.5) * v[j] + T(0.25) * from_right(v[j]);
+        T below = v[r - 1];
+#pragma unroll
+        for (int j = r; j < H - r; j++) {
+            const T f = T(0.25) * below + T(0.5) * v[j] + T(0.25) * v[j + 1];
+            below = v[j];
+            v[j] = f;
+        }
+    }
+    if (lane < P || lane >= 64 - P || x >= nx) return;
+#pragma unroll
+    for (int j = 0; j < FTY; j++)
+        if (Y0 + j < ny) dst[(size_t)(Y0 + j) * nx + x] += scale * v[P + j];
 }
 
 template <typename T>
@@ -225,11 +269,11 @@ dim3 grid3(int nx, int ny, int nz) { return dim3((nx + BXT - 1) / BXT, (ny + BYT
 
 template <typename T>
 hipError_t launch_adj_curlB(const Coef<T> &c, int ndim, int blocks, const T *const v[3],
-                            T *const Bbar[3], T sc, T *const acc[3], hipStream_t s)
+                            T *const Bbar[3], T sc, T *const acc[3], bool fresh, hipStream_t s)
 {
     hipLaunchKernelGGL((k_adj_curlB<T>), grid3(c.nx, c.ny, c.nz), dim3(NT), 0, s, c, ndim, blocks,
                        v[0], v[1], v[2], Bbar[0], Bbar[1], Bbar[2], sc, acc ? acc[0] : nullptr,
-                       acc ? acc[1] : nullptr, acc ? acc[2] : nullptr);
+                       acc ? acc[1] : nullptr, acc ? acc[2] : nullptr, fresh);
     return hipGetLastError();
 }
 
@@ -248,6 +292,22 @@ hipError_t launch_adj_source(const Coef<T> &c, int ndim, int passes, const T *co
                              T *const tmp1[3], T *const tmp2[3], T scale, T *const dJ0[3],
                              hipStream_t s)
 {
+    if (ndim == 2) {
+        const int ox = 64 - 2 * passes, oy = FTY * (NT / 64);
+        const dim3 g((c.nx + ox - 1) / ox, (c.ny + oy - 1) / oy, 3);
+        auto go = [&](auto k) {
+            hipLaunchKernelGGL(k, g, dim3(NT), 0, s, c.nx, c.ny, scale, v[0], v[1], v[2], dJ0[0], dJ0[1], dJ0[2]);
+        };
+        switch (passes) {
+        case 0: go(k_filter2_add<T, 0>); break;
+        case 1: go(k_filter2_add<T, 1>); break;
+        case 2: go(k_filter2_add<T, 2>); break;
+        case 3: go(k_filter2_add<T, 3>); break;
+        case 4: go(k_filter2_add<T, 4>); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     const int64_t n = (int64_t)c.nx * c.ny * c.nz;
     const unsigned nb = (unsigned)((n + NT - 1) / NT);
     for (int q = 0; q < 3; q++) {
@@ -293,7 +353,7 @@ hipError_t launch_axpy3(int64_t n, int mask, bool zero, T a, const T *const x[3]
 
 #define INST(T)                                                                                       \
     template hipError_t launch_adj_curlB<T>(const Coef<T> &, int, int, const T *const[3], T *const[3], \
-                                            T, T *const[3], hipStream_t);                             \
+                                            T, T *const[3], bool, hipStream_t);                       \
     template hipError_t launch_adj_curlE<T>(const Coef<T> &, int, int, const T *const[3], T *const[3], \
                                             hipStream_t);                                             \
     template hipError_t launch_adj_source<T>(const Coef<T> &, int, int, const T *const[3], T *const[3], \

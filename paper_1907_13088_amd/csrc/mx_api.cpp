@@ -1498,10 +1498,10 @@ int adjoint_impl(mx_grid *g, int nsteps, const double *env, const int *sweeps, v
     const int cmask = c.ndim == 3 ? 7 : ((c.blocks & 1) ? 3 : 0) | ((c.blocks & 2) ? 4 : 0);
     bool any_src = false;
     if (dJ0) {
-        // all three components start at zero: a block the grid does not step
-        // keeps a zero current gradient
-        ProfScope ps(g, MX_PROF_ADJOINT, arr * 3);
-        HIPCHK(launch_axpy3<T>(g->ncell, 7, true, T(0), acc, acc, g->stream));
+        // a block the grid does not step keeps a zero current gradient (the
+        // first step that adds to the others' sums starts them)
+        ProfScope ps(g, MX_PROF_ADJOINT, arr * (3 - __builtin_popcount(cmask)));
+        HIPCHK(launch_axpy3<T>(g->ncell, 7 & ~cmask, true, T(0), acc, acc, g->stream));
     }
     for (int s = nsteps - 1; s >= 0; s--) {
         int target[2] = {sweeps[2 * s], sweeps[2 * s + 1]};
@@ -1516,9 +1516,9 @@ int adjoint_impl(mx_grid *g, int nsteps, const double *env, const int *sweeps, v
         const bool add = dJ0 && sc != 0.0;
         {
             const int ncomp = __builtin_popcount(cmask);
-            ProfScope ps(g, MX_PROF_ADJOINT, arr * (9 + (add ? 2 * ncomp : 0)));
+            ProfScope ps(g, MX_PROF_ADJOINT, arr * (9 + (add ? (any_src ? 2 : 1) * ncomp : 0)));
             HIPCHK(launch_adj_curlB<T>(k, c.ndim, c.blocks, v, (T *const *)Bbar, (T)sc, add ? acc : nullptr,
-                                       g->stream));
+                                       !any_src, g->stream));
         }
         any_src = any_src || add;
         {
@@ -1527,8 +1527,8 @@ int adjoint_impl(mx_grid *g, int nsteps, const double *env, const int *sweeps, v
         }
     }
     if (any_src) {
-        // dJ0 += F acc; filter temporaries: dE' and the running-sum buffers
-        ProfScope ps(g, MX_PROF_ADJOINT, arr * 3 * (2 * c.ndim * c.filter_passes + 3));
+        // dJ0 += F acc; filter temporaries (3D): dE' and the running-sum buffers
+        ProfScope ps(g, MX_PROF_ADJOINT, arr * 3 * ((c.ndim == 2 ? 0 : 2 * c.ndim * c.filter_passes) + 3));
         HIPCHK(launch_adj_source<T>(k, c.ndim, c.filter_passes, (const T *const *)acc, (T *const *)g->dEp,
                                     (T *const *)g->S, T(1), (T *const *)dJ0, g->stream));
     }

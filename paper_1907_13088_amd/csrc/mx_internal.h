@@ -114,6 +114,25 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// value of the lane one column to the left or right (zero where the wave has none)
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_dpp(double v)
+{
+    const long long u = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+template <typename T>
+__device__ __forceinline__ T from_left(T v) { return lane_dpp<0x138>(v); }    // wave_shr:1, lane - 1
+template <typename T>
+__device__ __forceinline__ T from_right(T v) { return lane_dpp<0x130>(v); }   // wave_shl:1, lane + 1
+
 // One value of an array of `bytes` bytes, `at` bytes from its start.  From
 // BUF_DROP, as from any offset past the end, a load gives zero and a store is
 // dropped (bounds check of raw buffers), so lanes without work need no branch
@@ -452,7 +471,7 @@ hipError_t launch_tol_decide(TolState *st, const double *red, int b, int k, int 
 // is set
 template <typename T>
 hipError_t launch_adj_curlB(const Coef<T> &c, int ndim, int blocks, const T *const v[3],
-                            T *const Bbar[3], T sc, T *const acc[3], hipStream_t s);
+                            T *const Bbar[3], T sc, T *const acc[3], bool fresh, hipStream_t s);
 template <typename T>
 hipError_t launch_adj_curlE(const Coef<T> &c, int ndim, int blocks, const T *const Bbar[3],
                             T *const Ebar[3], hipStream_t s);
