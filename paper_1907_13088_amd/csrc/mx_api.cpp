@@ -147,7 +147,6 @@ struct mx_grid {
     void *D2[3];          // Chebyshev solve: the increment buffer paired with S
     int bloc[3];          // 2D: where component q of B currently lives (0 user, 1 workspace)
     double *partial;      // device
-    double *red;          // device, 2 doubles
     double *hred = nullptr;   // pinned host memory for read-backs (a TolState)
     TolState hbuf;            // pageable read-back target when hred is not set
     // single-launch small-grid solve: device areas in the workspace, and
@@ -355,8 +354,6 @@ static void grid_setup(mx_grid *g, const mx_config *cfg, hipStream_t stream, int
     }
     g->partial = (double *)p;
     p += up((size_t)max_wg(cfg) * 2 * sizeof(double));
-    g->red = (double *)p;
-    p += up(8 * sizeof(double));
     g->tol = (TolState *)p;
     p += up(sizeof(TolState));
     g->small_env = nullptr;
@@ -452,7 +449,7 @@ int mx_workspace_size(const mx_config *c, size_t *bytes)
     if (rc) return rc;
     if (!bytes) return fail(MX_EINVAL, "bytes is NULL");
     const size_t arr = up((size_t)ncell_of(c) * elem_of(c));
-    *bytes = n_arrays(c) * arr + up((size_t)max_wg(c) * 2 * sizeof(double)) + up(8 * sizeof(double)) +
+    *bytes = n_arrays(c) * arr + up((size_t)max_wg(c) * 2 * sizeof(double)) +
              up(sizeof(TolState)) + (c->ndim == 2 ? small_area() : 0);
     return MX_OK;
 }
@@ -720,8 +717,7 @@ int solve_tol(mx_grid *g, void *const rhs[3], const int *target_in, const T **re
                 if (e != hipSuccess) return fail(MX_EDEVICE, "sweep launch: %s", hipGetErrorString(e));
                 {
                     ProfScope ps(g, MX_PROF_OTHER, 0.0);
-                    HIPCHK(launch_reduce2(g->partial, nwg, g->red, g->stream, skip));
-                    HIPCHK(launch_tol_decide(g->tol, g->red, b, kk, ob, c.tol, g->stream));
+                    HIPCHK(launch_tol_decide(g->tol, g->partial, nwg, b, kk, ob, c.tol, g->stream));
                 }
                 enq[b]++;
                 swe[b] += kk;
@@ -1445,8 +1441,7 @@ int step_impl(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
         if (tolmode) {
             // ||dE'|| per block starts the device-side state of the solve
             ProfScope ps(g, MX_PROF_OTHER, 0.0);
-            HIPCHK(launch_reduce2(g->partial, nwg, g->red, g->stream));
-            HIPCHK(launch_tol_init(g->tol, g->red, nblk, g->stream));
+            HIPCHK(launch_tol_init(g->tol, g->partial, nwg, nblk, g->stream));
         }
         const T *res[3];
         bool e_done[2] = {false, false};

@@ -458,13 +458,13 @@ template <typename T>
 hipError_t launch_sweep3d(const Coef<T> &c, int k, int form, int flags, const SweepArgs<T> &a,
                           hipStream_t s, int *nwg);
 
-// FP64 partial-sum reduction: out[0..1] = sum over nwg rows of partial[row][0..1]
-hipError_t launch_reduce2(const double *partial, int nwg, double *out, hipStream_t s, const int *skip = nullptr);
+// Both sum the nwg rows of partial[row][0..1] (FP64, fixed order)
 // tolerance solve state: start a step from the reduced ||dE'||^2 per block
-hipError_t launch_tol_init(TolState *st, const double *red, int nblk, hipStream_t s);
+hipError_t launch_tol_init(TolState *st, const double *partial, int nwg, int nblk, hipStream_t s);
 // after a pass of k sweeps of block b that wrote iterate buffer buf: the
 // reduced step norm, the stop test against tol * ||dE'||
-hipError_t launch_tol_decide(TolState *st, const double *red, int b, int k, int buf, double tol, hipStream_t s);
+hipError_t launch_tol_decide(TolState *st, const double *partial, int nwg, int b, int k, int buf, double tol,
+                             hipStream_t s);
 
 // Adjoint helpers (kadj.hip)
 // Bbar += dt Lambda K v, and acc += sc v on the stepped components when acc
