@@ -346,7 +346,11 @@ int mx_sources_project(mx_grid *g, int nsrc, int W, const int64_t *origins, cons
  * first config deep (capped at 7); mx_batch_init with sweeps_per_pass = 0
  * times candidate pass depths and chunk lengths on workspace scratch
  * fields (the bound state is never touched), separately for the grouped
- * and the persistent schedule, and keeps the fastest of each.  The chosen
+ * and the persistent schedule, and keeps the fastest of each.  With
+ * sweeps_per_pass = 0 the grouped schedule of a batch of up to 3.4 (FP32; 2.9
+ * with fewer than 12 sweeps) or 7.3 (FP64) million cells runs on register
+ * tiles instead, as single grids do (variant 0); the results are the same
+ * bitwise.  The chosen
  * plans are kept in a text file and reused by a later init of the same
  * grid configs on the same device and library build: $MX_TUNE_CACHE (a
  * path; "0" or empty turns the cache off), else
@@ -360,9 +364,10 @@ int mx_batch_init(const mx_config *cfgs, int ngrids, void *stream, void *workspa
                   size_t workspace_bytes, mx_batch **out);
 int mx_batch_bind(mx_batch *b, int grid, void *const E[3], void *const B[3]);
 int mx_batch_step(mx_batch *b, int nsteps, int persistent);
-/* The schedules in use: sweeps per pass of the grouped schedule (tuned at
-   init when the configs ask for sweeps_per_pass = 0), its total work items
-   of one step, and the workgroups of the persistent launch. */
+/* The row-streaming schedules: sweeps per pass of the grouped schedule (tuned
+   at init when the configs ask for sweeps_per_pass = 0; batches that run on
+   register tiles do not use it), its total work items of one step, and the
+   workgroups of the persistent launch. */
 int mx_batch_get_plan(mx_batch *b, int *sweeps_per_pass, int *tiles_total, int *persistent_blocks);
 /* One schedule's tuned shape (persistent = 0 grouped, 1 persistent): the
    deepest pass (sweeps), the rows of a sweep work item's chunk and of a

@@ -226,6 +226,55 @@ RegPlan reg_plan(bool f64, int blocks, bool cheb, bool front, int64_t nx, int64_
     return best;
 }
 
+// Batches by register tiles against row streams, by their cells, us per step.
+// FP32: 1.3 million, 14 sweeps, 72 against 107; 2.75 million, 20 sweeps, 134
+// against 155; 3.3 million, 20 sweeps, 162 against 192, but with 8 sweeps 2.9
+// million 83 against 87 and with 10 sweeps 98 against 97; 4.5 million, 20
+// sweeps, 218 against 216.  FP64: 0.18 million, 12 sweeps, 30 against 123; 4.3
+// million, 20 sweeps, 367 against 485, 8 sweeps 250 against 255; 7.2 million
+// 587 against 770 and 395 against 413.
+static bool reg_batch_pays(bool f64, int m, int64_t cells)
+{
+    return cells <= (f64 ? (int64_t)14 << 19 : (int64_t)(m >= 12 ? 13 : 11) << 18);
+}
+
+int64_t reg_batch_tiles(int geo, int kind, int cut, int64_t nx, int64_t ny)
+{
+    return reg2d::tiles(reg2d::GEO[geo], kind, cut, nx, ny);
+}
+
+RegBatchPlan reg_batch_plan(const mx_config *cfgs, int ng)
+{
+    using namespace reg2d;
+    const bool f64 = cfgs[0].dtype == MX_F64;
+    const int m = cfgs[0].sweeps;
+    int64_t cells = 0;
+    for (int i = 0; i < ng; i++) cells += cfgs[i].n[0] * cfgs[i].n[1];
+    RegBatchPlan best{-1, 0, 0, 0};
+    if (!reg_batch_pays(f64, m, cells)) return best;
+    double us = 1e29;
+    const Fit *fit = FIT[0][f64 ? 5 : 2];
+    for (int g = 0; g < 3; g++) {
+        const int kmax = std::min((GEO[g].ry - 4) / 2, 16);
+        for (int n = std::max(2, (m + kmax - 1) / kmax); n <= m / 2 + 2; n++) {
+            // passes of m / n sweeps, the first ones one fewer than the rest
+            const int kf = m / n, ks = (m + n - 1) / n;
+            auto pass = [&](int kind, int k) {
+                const int W = GEO[g].rx - 2 * k - (kind == RK_FRONT ? 3 : 0), H = GEO[g].ry - 2 * k;
+                if (W < 12 || H < 4) return 1e30;
+                double t = 0.0;
+                for (int i = 0; i < ng; i++) t += 2.0 * tiles(GEO[g], kind, k, cfgs[i].n[0], cfgs[i].n[1]);
+                const double c = per_cu(t);
+                return fit[g].t0 + c * fit[g].load[kind] + k * (c * fit[g].s + fit[g].s0);
+            };
+            const double t = pass(RK_FRONT, kf) + (n - 2) * pass(RK_MID, ks) + pass(RK_LAST, ks);
+            if (t < us) us = t, best = RegBatchPlan{g, n, kf, ks};
+            if (n > 40) break;
+        }
+    }
+    return best;
+}
+
 RegPlan reg_tol_plan(bool f64, int blocks, bool cheb, int64_t nx, int64_t ny, int k, int64_t stride)
 {
     using namespace reg2d;

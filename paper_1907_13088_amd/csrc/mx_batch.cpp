@@ -95,6 +95,7 @@ struct mx_batch {
     int pk, pLf, pLs;                  // persistent schedule: the same
     int nf, ns;                        // items per phase (of the last upload)
     bool tuned;
+    RegBatchPlan reg;                  // register-tile passes of the grouped schedule (geo < 0: row streams)
 };
 
 namespace {
@@ -133,7 +134,7 @@ void persistent_shape(int m, int k, int *q, int *npass, int *nlow)
 }
 
 template <typename T>
-int upload(mx_batch *b, bool scratch_fields, int k, int Lf, int Ls)
+int upload(mx_batch *b, bool scratch_fields, int k, int Lf, int Ls, bool reg = false)
 {
     // Descriptors and item tables for a schedule of passes at most k deep
     // and chunks of Lf (front) and Ls (sweeps) rows.  With scratch_fields
@@ -166,6 +167,10 @@ int upload(mx_batch *b, bool scratch_fields, int k, int Lf, int Ls)
         gd.nsx_s = (nx + wsw - 1) / wsw;
         itf[g + 1] = itf[g] + gd.nsx_f * ((ny + Lf - 1) / Lf);
         its[g + 1] = its[g] + gd.nsx_s * ((ny + Ls - 1) / Ls);
+        if (reg) {
+            itf[g + 1] = itf[g] + (int)reg_batch_tiles(b->reg.geo, RK_FRONT, b->reg.kf, nx, ny);
+            its[g + 1] = its[g] + (int)reg_batch_tiles(b->reg.geo, RK_MID, b->reg.ks, nx, ny);
+        }
     }
     b->nf = itf[b->ng];
     b->ns = its[b->ng];
@@ -204,6 +209,30 @@ int grouped_steps(mx_batch *b, int nsteps, int bin0)
                                           (int)((p + 1) & 1), (int)(p & 1), b->stream));
         }
     }
+    return MX_OK;
+}
+
+// nsteps steps on register tiles: per step the front's pass, then the others;
+// the last pass of an odd count hands B back
+template <typename T>
+int reg_batch_steps(mx_batch *b, int nsteps)
+{
+    const GridDesc<T> *d = (const GridDesc<T> *)b->desc;
+    const RegBatchPlan &r = b->reg;
+    for (int s = 0; s < nsteps; s++)
+        for (int p = 0, rem = b->m; p < r.passes; p++) {
+            RegBatchPass a{};
+            a.kind = p == 0 ? RK_FRONT : (p + 1 == r.passes ? RK_LAST : RK_MID);
+            a.k = rem / (r.passes - p);
+            a.cut = p == 0 ? r.kf : r.ks;
+            a.first = p == 0;
+            a.bin = s & 1;
+            a.xout = p & 1;
+            a.hand = a.kind == RK_LAST && s + 1 == nsteps && nsteps % 2 == 1;
+            rem -= a.k;
+            BCHK(launch_reg_batch<T>(d, b->ng, p == 0 ? b->items_f : b->items_s, p == 0 ? b->nf : b->ns, r.geo, a,
+                                     b->stream));
+        }
     return MX_OK;
 }
 
@@ -510,6 +539,8 @@ int mx_batch_init(const mx_config *cfgs, int ngrids, void *stream, void *workspa
     b->spp = b->pk = cfgs[0].sweeps_per_pass > 0 ? std::min(cfgs[0].sweeps_per_pass, batch2d::KMAX) : 5;
     b->Lf = b->Ls = b->pLf = b->pLs = 64;
     b->tuned = false;
+    b->reg = RegBatchPlan{-1, 0, 0, 0};
+    if (cfgs[0].sweeps_per_pass == 0) b->reg = reg_batch_plan(cfgs, ngrids);
     if (cfgs[0].sweeps_per_pass == 0) {
         const std::string path = tune_cache_path();
         const uint64_t key = tune_key(b);
@@ -549,6 +580,11 @@ int mx_batch_step(mx_batch *b, int nsteps, int persistent)
     if (persistent) {
         rc = f64 ? upload<double>(b, false, b->pk, b->pLf, b->pLs) : upload<float>(b, false, b->pk, b->pLf, b->pLs);
         if (!rc) rc = f64 ? persistent_steps<double>(b, nsteps, 0) : persistent_steps<float>(b, nsteps, 0);
+    } else if (b->reg.geo >= 0) {
+        rc = f64 ? upload<double>(b, false, b->spp, b->Lf, b->Ls, true)
+                 : upload<float>(b, false, b->spp, b->Lf, b->Ls, true);
+        if (!rc) rc = f64 ? reg_batch_steps<double>(b, nsteps) : reg_batch_steps<float>(b, nsteps);
+        return rc;
     } else {
         rc = f64 ? upload<double>(b, false, b->spp, b->Lf, b->Ls) : upload<float>(b, false, b->spp, b->Lf, b->Ls);
         if (!rc) rc = f64 ? grouped_steps<double>(b, nsteps, 0) : grouped_steps<float>(b, nsteps, 0);

@@ -362,6 +362,25 @@ hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, int form,
                       int *npart);
 template <typename T>
 hipError_t launch_reg_finish(const RegFinish<T> &f, hipStream_t s);
+// The same passes over the grids of a batch, both blocks, fixed counts
+// (k2r_batch.hip).  kf: sweeps of the front's pass; ks: of the deepest other
+struct RegBatchPlan {
+    int geo, passes, kf, ks;
+};
+// geo < 0: the row streams are faster
+RegBatchPlan reg_batch_plan(const mx_config *cfgs, int ng);
+// tiles of a grid in a pass of `kind` cut for `cut` sweeps
+int64_t reg_batch_tiles(int geo, int kind, int cut, int64_t nx, int64_t ny);
+struct RegBatchPass {
+    int kind, k, cut;   // sweeps, and the sweeps its tiles are cut for
+    int first;          // no sweeps before: the iterate is dE'
+    int bin;            // B buffer the front reads
+    int xout;           // iterate buffer written (read: the other one)
+    int hand;           // last pass: hand B back from the workspace
+};
+template <typename T>
+hipError_t launch_reg_batch(const GridDesc<T> *d, int ng, const int *tiles, int n, int geo, const RegBatchPass &p,
+                            hipStream_t s);
 // out = p binomial passes per axis of the components of mask (2D); nothing
 // where *stall equals epoch (stall null: always)
 template <typename T>
