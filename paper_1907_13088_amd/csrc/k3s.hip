@@ -366,9 +366,9 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
     for (; t < tout; t++) step(t, std::false_type{});
     // pairs of steps let the values carried from plane to plane change their
     // registers instead of being moved (512^3 FP32: 7.5 against 7.7 ms per
-    // step); the delta form, which stores twice as much, is faster without
-    // (33.4 against 35.9)
-    if constexpr (DELTA) {
+    // step); the FP32 delta form, which stores twice as much, is faster
+    // without (33.4 against 35.9; FP64 89.5 with, 90.9 without)
+    if constexpr (DELTA && sizeof(T) == 4) {
         for (; t < tend; t++) step(t, std::true_type{});
     } else {
         for (; t < tend; t += 2) {
