@@ -389,7 +389,7 @@ def bench_planewave_te(steps, warm):
                  {"steps": steps, "repeats": 5, "us_per_step": round(dt / steps * 1e6, 1),
                   "us_per_step_range": [round(min(times) / steps * 1e6, 1), round(max(times) / steps * 1e6, 1)],
                   "mean_sweeps": round(sweeps, 1), "sweeps_per_pass": g.sweeps_per_pass, "dtype": "f64",
-                  "note": "latency bound: one cooperative launch runs up to 64 steps, the stop test on the device; "
+                  "note": "latency bound: up to 64 steps queued ahead of the host, the stop test on the device; "
                           "the median of 5 repeats"})
 
 

@@ -117,9 +117,10 @@ typedef struct mx_config {
                              million cells by dtype, blocks and solve: register
                              tiles, which cut a fixed count into passes by a
                              time model of their own and a tolerance solve at
-                             the depths below; else FP32: 4, FP64 and the Chebyshev solve: 3; Alg 1 on
-                             a grid whose streaming pass would have fewer
-                             workgroups than half the CUs: 1),
+                             the depths below; else FP32: 4, FP64 and the
+                             Chebyshev solve: 3; Alg 1 on a grid whose
+                             streaming pass would have fewer workgroups than
+                             half the CUs: 1),
                              1 LDS tile (both blocks per pass; by default 5
                              sweeps deep in FP32, 4 in FP64, 8 under a
                              tolerance), 2 row streaming
@@ -197,11 +198,11 @@ int mx_set_step(mx_grid *g, int64_t n);
 
 /* Sweeps fused per HBM pass in use (the library's or the configured choice;
    of the row-streaming or LDS-tile kernel, and of tolerance solves on register
-   tiles, not of their fixed counts): that of the TE block when it is active, else that of TM.  With a fixed m
-   a block's m sweeps run in the fewest passes of at most this depth, of
-   nearly equal depth, the deeper ones last; under a tolerance the stop
-   test follows every pass, and both 2D blocks then use one depth unless
-   sweeps_per_pass is capped. */
+   tiles, not of their fixed counts): that of the TE block when it is active,
+   else that of TM.  With a fixed m a block's m sweeps run in the fewest passes
+   of at most this depth, of nearly equal depth, the deeper ones last; under a
+   tolerance the stop test follows every pass, and both 2D blocks then use one
+   depth unless sweeps_per_pass is capped. */
 int mx_get_sweeps_per_pass(mx_grid *g, int *k);
 
 /* Sweeps per pass of each 2D block: k[0] TE, k[1] TM (3D: k[0]). */
