@@ -1,5 +1,5 @@
 // Register-tile passes of the 2D step: choice of tile and depth, dispatch
-// (the kernels are instantiated in k2r_{f32,f64}_{te,tm,all}.hip), and the
+// (the kernels are instantiated in k2r_{f32,f64}_{std,tol,cheb,ctol}.hip), and the
 // filter of the current that runs once per call ahead of them.
 #include <algorithm>
 #include <cmath>

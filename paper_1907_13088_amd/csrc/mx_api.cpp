@@ -1496,7 +1496,7 @@ int adjoint_impl(mx_grid *g, int nsteps, const double *env, const int *sweeps, v
         // a block the grid does not step keeps a zero current gradient (the
         // first step that adds to the others' sums starts them)
         ProfScope ps(g, MX_PROF_ADJOINT, arr * (3 - __builtin_popcount(cmask)));
-        HIPCHK(launch_axpy3<T>(g->ncell, 7 & ~cmask, true, T(0), acc, acc, g->stream));
+        HIPCHK(launch_zero3<T>(g->ncell, 7 & ~cmask, acc, g->stream));
     }
     for (int s = nsteps - 1; s >= 0; s--) {
         int target[2] = {sweeps[2 * s], sweeps[2 * s + 1]};

@@ -503,6 +503,6 @@ hipError_t launch_sources(int nx, int ny, int nsrc, int W, const int64_t *origin
                           const T *amps, T *const J0[3], T *const G[3], T *grad, bool project,
                           hipStream_t s);
 template <typename T>
-hipError_t launch_axpy3(int64_t n, int mask, bool zero, T a, const T *const x[3], T *const acc[3], hipStream_t s);
+hipError_t launch_zero3(int64_t n, int mask, T *const acc[3], hipStream_t s);
 
 }  // namespace mx
