@@ -847,8 +847,11 @@ int reg_filter(mx_grid *g, void *const out[3], const int *stall = nullptr, int e
 // modelled faster (on the largest grids one after the other keeps more of
 // their arrays in the last-level cache: 2048^2 FP64, 20 sweeps, 299 against
 // 340 us).
+// jf (Chebyshev steps with a filtered current): per block, whether X[1]
+// still holds the filtered current of its components.
 template <typename T>
-int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int target[2], const T **res)
+int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int target[2], const T **res,
+              bool *jf = nullptr)
 {
     const mx_config &c = g->cfg;
     const Coef<T> &k = coef<T>(g);
@@ -871,12 +874,13 @@ int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int
         const RegPlan &p = reg_plan_of(g, blk, fr, m);
         const int ncomp = blk == 3 ? 3 : (blk == 1 ? 2 : 1);
         const double arr = (double)g->ncell * sizeof(T);
-        // filtered current of the front: where the pass's own buffers leave
-        // room (the Chebyshev increments take S)
-        const bool filt = front && g->has_j && c.filter_passes > 0;
-        if (filt && cheb && p.passes > 2) {
+        // the front reads the filtered current in X[1] (S holds the
+        // increments): filtered again where a step's second pass wrote there
+        const bool lost = jf && ((blk & 1 && !jf[0]) || (blk & 2 && !jf[1]));
+        if (lost) {
             const int rc = reg_filter<T>(g, g->X[1]);
             if (rc) return rc;
+            jf[0] = jf[1] = true;
         }
         for (int i = 0, rem = m; i < p.passes; i++) {
             const int kind = front && i == 0 ? RK_FRONT : (front && i == p.passes - 1 ? RK_LAST : RK_MID);
@@ -897,6 +901,9 @@ int reg_solve(mx_grid *g, const RegArgs<T> *front, void *const rhs[3], const int
             }
             if (e != hipSuccess) return fail(MX_EDEVICE, "register-tile pass: %s", hipGetErrorString(e));
             rem -= a.k;
+            if (jf && ob == 1 && kind != RK_LAST)   // the iterate went to X[1]
+                for (int b = 0; b < 2; b++)
+                    if (blk & (1 << b)) jf[b] = false;
             if (!front)
                 for (int q = 0; q < 3; q++)
                     if (blk & (q == 2 ? 2 : 1)) res[q] = (const T *)g->X[ob][q];
@@ -912,12 +919,14 @@ int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
     const mx_config &c = g->cfg;
     // the current's filter is the same at every step of the call: applied
     // once, into S (fixed counts of Alg 1 keep no running sum) or, for the
-    // Chebyshev solve, X[1] (free in steps of two passes; deeper ones filter
-    // each step, in reg_solve)
+    // Chebyshev solve, X[1], where a step of more than two passes writes its
+    // iterate: reg_solve filters it there whenever a front would not find it
     void *const *Jf = g->J0;
-    if (g->has_j && c.filter_passes > 0 && nsteps > 0) {
-        Jf = c.solver == MX_SOLVER_CHEBYSHEV ? g->X[1] : g->S;
-        const int rc = reg_filter<T>(g, Jf);
+    bool jf[2] = {false, false};
+    const bool filt = g->has_j && c.filter_passes > 0, cheb = c.solver == MX_SOLVER_CHEBYSHEV;
+    if (filt && nsteps > 0) {
+        Jf = cheb ? g->X[1] : g->S;
+        const int rc = cheb ? MX_OK : reg_filter<T>(g, Jf);
         if (rc) return rc;
     }
     for (int s = 0; s < nsteps; s++) {
@@ -941,7 +950,7 @@ int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
                 g->bloc[q] = 0;
             }
         }
-        const int rc = reg_solve<T>(g, &a, g->dEp, target, nullptr);
+        const int rc = reg_solve<T>(g, &a, g->dEp, target, nullptr, filt && cheb ? jf : nullptr);
         if (rc) return rc;
         if (stats) {
             stats[s] = mx_step_stats{};
