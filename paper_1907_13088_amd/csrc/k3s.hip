@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "mx_internal.h"
+#include "plan3d.h"
 #include "stencil2d.h"
 
 namespace mx {
@@ -413,31 +414,6 @@ Zc<T> zcoef(const Coef<T> &c)
     return z;
 }
 
-// A launch's z chunks and its time in the model that sizes it: a workgroup
-// marches Lz + 3K plane steps (its chunk and the pipeline's fill and drain),
-// the workgroups run in rounds of one per CU, and a step costs its rows plus
-// about 8 (the barrier and the latencies of a step on a CU that is not full;
-// fitted on 64^3 to 512^3).  Chunks of two planes pay on small grids, where
-// they are what fills the CUs.
-struct Split {
-    int gx, gy, Lz, nzc;
-    double cost;
-};
-
-template <int K, int R, int NW>
-Split split(int nx, int ny, int nz, int cus)
-{
-    constexpr int OX = 64 - 2 * K, OY = NW * R - 2 * (K - 1);
-    Split best{(nx + OX - 1) / OX, (ny + OY - 1) / OY, nz, 1, 1e300};
-    const int64_t ncol = (int64_t)best.gx * best.gy;
-    for (int n = 1; n <= std::max(1, nz / 2); n++) {
-        const int Lz = (nz + n - 1) / n, nzc = (nz + Lz - 1) / Lz;
-        const double cost = (double)((ncol * nzc + cus - 1) / cus) * (Lz + 3 * K) * (NW * R + 8);
-        if (cost < best.cost * (1.0 - 1e-9)) best.cost = cost, best.Lz = Lz, best.nzc = nzc;
-    }
-    return best;
-}
-
 inline int cu_count()
 {
     static std::atomic<int> cache[MX_MAX_DEVICES];
@@ -451,10 +427,13 @@ inline int cu_count()
 }
 
 template <typename T, int K, int FORM, bool LAST, int R, int NW>
-hipError_t launch_k(const Coef<T> &c, const Split &p, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+hipError_t launch_k(const Coef<T> &c, const plan3d::Split &p, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
 {
+    static_assert(K <= plan3d::kmax(sizeof(T) == 8) && plan3d::out_x(K) == 64 - 2 * K);
     dim3 g(p.gx, p.gy, p.nzc);
     *nwg = g.x * g.y * g.z;
+    // a workgroup leaves its partial sums in a row of its own
+    if (*nwg > plan3d::partial_rows(sizeof(T) == 8, c.nx, c.ny, c.nz)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k3_stream<T, K, FORM, LAST, R, NW>), g, dim3(64 * NW), 0, s, c, zcoef(c), a, flags, p.Lz);
     return hipGetLastError();
 }
@@ -472,16 +451,16 @@ hipError_t launch_k(const Coef<T> &c, const Split &p, int flags, const SweepArgs
 template <typename T, int K, int FORM, bool LAST>
 hipError_t launch_shape(const Coef<T> &c, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
 {
-    constexpr bool F32 = sizeof(T) == 4;
+    constexpr bool F64 = sizeof(T) == 8;
     if constexpr (FORM == FM_CHEB) {
-        constexpr int NW = F32 ? 16 : 12;
-        return launch_k<T, K, FORM, LAST, 1, NW>(c, split<K, 1, NW>(c.nx, c.ny, c.nz, cu_count()), flags, a, s, nwg);
+        constexpr plan3d::Shape S = plan3d::cheb(F64);
+        return launch_k<T, K, FORM, LAST, S.r, S.nw>(c, plan3d::split(S, K, c.nx, c.ny, c.nz, cu_count()), flags, a, s, nwg);
     } else {
-        constexpr int NL = F32 ? 12 : 8, NS = F32 ? 8 : 4;
-        const Split l = split<K, 2, NL>(c.nx, c.ny, c.nz, cu_count());
-        const Split m = split<K, 2, NS>(c.nx, c.ny, c.nz, cu_count());
-        if (m.cost < l.cost) return launch_k<T, K, FORM, LAST, 2, NS>(c, m, flags, a, s, nwg);
-        return launch_k<T, K, FORM, LAST, 2, NL>(c, l, flags, a, s, nwg);
+        constexpr plan3d::Shape SL = plan3d::large(F64), SS = plan3d::small(F64);
+        const plan3d::Split l = plan3d::split(SL, K, c.nx, c.ny, c.nz, cu_count());
+        const plan3d::Split m = plan3d::split(SS, K, c.nx, c.ny, c.nz, cu_count());
+        if (m.cost < l.cost) return launch_k<T, K, FORM, LAST, SS.r, SS.nw>(c, m, flags, a, s, nwg);
+        return launch_k<T, K, FORM, LAST, SL.r, SL.nw>(c, l, flags, a, s, nwg);
     }
 }
 
@@ -507,7 +486,7 @@ hipError_t launch_last(const Coef<T> &c, int k, int flags, const SweepArgs<T> &a
 
 }  // namespace
 
-int stream3d_kmax(bool f64) { return f64 ? 2 : 3; }
+int stream3d_kmax(bool f64) { return plan3d::kmax(f64); }
 
 template <typename T>
 hipError_t launch_stream3d(const Coef<T> &c, int k, int form, int flags, const SweepArgs<T> &a, hipStream_t s,

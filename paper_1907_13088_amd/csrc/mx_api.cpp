@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "mx_internal.h"
+#include "plan3d.h"
 
 using namespace mx;
 
@@ -46,12 +47,14 @@ size_t elem_of(const mx_config *c) { return c->dtype == MX_F64 ? 8 : 4; }
 int64_t max_wg(const mx_config *c)
 {
     const int64_t nx = c->n[0], ny = c->n[1], nz = c->ndim == 3 ? c->n[2] : 1;
-    // 2D front tiles 64x16, 2D sweep tiles 64x8 at the smallest, 3D 64x4 per plane
+    // 2D front tiles 64x16, 2D sweep tiles 64x8 at the smallest, 3D front 64x4 per plane
     const int64_t a = ((nx + 63) / 64) * ((ny + 3) / 4) * nz;
     // the streaming sweep launches at most one workgroup per (strip, row);
     // strips are at least 256 - 2 * 16 columns wide
     const int64_t b = ((nx + 223) / 224 + 1) * ny;
-    return std::max(a, b);
+    // 3D sweep passes: narrower tiles, in chunks of two planes or more
+    const int64_t s = c->ndim == 3 ? plan3d::partial_rows(c->dtype == MX_F64, nx, ny, nz) : 0;
+    return std::max({a, b, s});
 }
 
 // Sweeps per pass of each 2D block (TE, TM).  The LDS-tile kernel (variant

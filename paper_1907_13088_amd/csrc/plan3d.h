@@ -1,0 +1,67 @@
+#pragma once
+// How a 3D sweep pass (k3s.hip) is cut into workgroups, and how many rows of
+// partial sums that takes.  Host code without HIP, so that the workspace, the
+// launch and a CPU test go by the same rules.
+#include <algorithm>
+#include <cstdint>
+
+namespace mx {
+namespace plan3d {
+
+// deepest pass
+constexpr int kmax(bool f64) { return f64 ? 2 : 3; }
+
+// Tiles: R rows per wave, NW waves (launch_shape in k3s.hip chooses): the
+// larger and the smaller one of Alg 1 and the delta form, and that of the
+// Chebyshev form
+struct Shape {
+    int r, nw;
+};
+constexpr Shape large(bool f64) { return {2, f64 ? 8 : 12}; }
+constexpr Shape small(bool f64) { return {2, f64 ? 4 : 8}; }
+constexpr Shape cheb(bool f64) { return {1, f64 ? 12 : 16}; }
+
+// A launch's z chunks and its time in the model that sizes it: a workgroup
+// marches Lz + 3K plane steps (its chunk and the pipeline's fill and drain),
+// the workgroups run in rounds of one per CU, and a step costs its rows plus
+// about 8 (the barrier and the latencies of a step on a CU that is not full;
+// fitted on 64^3 to 512^3).  Chunks of two planes pay on small grids, where
+// they are what fills the CUs.
+struct Split {
+    int gx, gy, Lz, nzc;
+    double cost;
+};
+
+// output columns and rows of a tile in a pass of k sweeps
+constexpr int out_x(int k) { return 64 - 2 * k; }
+constexpr int out_y(Shape s, int k) { return s.nw * s.r - 2 * (k - 1); }
+
+inline Split split(Shape s, int k, int nx, int ny, int nz, int cus)
+{
+    const int ox = out_x(k), oy = out_y(s, k);
+    Split best{(nx + ox - 1) / ox, (ny + oy - 1) / oy, nz, 1, 1e300};
+    const int64_t ncol = (int64_t)best.gx * best.gy;
+    for (int n = 1; n <= std::max(1, nz / 2); n++) {
+        const int Lz = (nz + n - 1) / n, nzc = (nz + Lz - 1) / Lz;
+        const double cost = (double)((ncol * nzc + cus - 1) / cus) * (Lz + 3 * k) * (s.nw * s.r + 8);
+        if (cost < best.cost * (1.0 - 1e-9)) best.cost = cost, best.Lz = Lz, best.nzc = nzc;
+    }
+    return best;
+}
+
+// Rows of partial sums (one per workgroup) of any pass on this grid, whatever
+// the number of CUs: the tiles of the narrowest and lowest output, times the
+// most chunks.
+inline int64_t partial_rows(bool f64, int64_t nx, int64_t ny, int64_t nz)
+{
+    int64_t rows = 0;
+    for (int k = 1; k <= kmax(f64); k++)
+        for (const Shape s : {large(f64), small(f64), cheb(f64)}) {
+            const int ox = out_x(k), oy = out_y(s, k);
+            rows = std::max(rows, ((nx + ox - 1) / ox) * ((ny + oy - 1) / oy) * std::max<int64_t>(1, nz / 2));
+        }
+    return rows;
+}
+
+}  // namespace plan3d
+}  // namespace mx
