@@ -492,7 +492,7 @@ template <typename T>
 hipError_t launch_stream3d(const Coef<T> &c, int k, int form, int flags, const SweepArgs<T> &a, hipStream_t s,
                            int *nwg)
 {
-    if (k < 1 || k > stream3d_kmax(sizeof(T) == 8)) return hipErrorInvalidValue;
+    if (k < 1 || k > stream3d_kmax(sizeof(T) == 8) || !plan3d::row_fits(c.nx, sizeof(T))) return hipErrorInvalidValue;
     if (form == FM_CHEB) return launch_last<T, FM_CHEB>(c, k, flags, a, s, nwg);
     if (form == FM_DELTA) return launch_last<T, FM_DELTA>(c, k, flags, a, s, nwg);
     return launch_last<T, FM_STD>(c, k, flags, a, s, nwg);

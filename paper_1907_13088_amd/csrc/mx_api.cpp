@@ -1364,6 +1364,8 @@ int step_impl(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
             if (!replay && c.lumped) target[b] = 0;
             if (target[b] < 0) return fail(MX_EINVAL, "negative replayed sweep count at step %d", s);
         }
+        if (c.ndim == 3 && target[0] > 0 && !plan3d::row_fits(c.n[0], sizeof(T)))
+            return fail(MX_EINVAL, "the sweeps of 3D grids take rows below 4 GiB (n[0] = %lld)", (long long)c.n[0]);
         // the front runs fused with the first sweep pass when both blocks
         // take the same count of Alg 1 sweeps in more than one pass and that
         // first pass's depth has a fused kernel

@@ -3,6 +3,7 @@
 // partial sums that takes.  Host code without HIP, so that the workspace, the
 // launch and a CPU test go by the same rules.
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 namespace mx {
@@ -10,6 +11,10 @@ namespace plan3d {
 
 // deepest pass
 constexpr int kmax(bool f64) { return f64 ? 2 : 3; }
+
+// A row of the grid is one buffer of 32-bit byte offsets, the last of which
+// (0xffffffff) stands for "no cell"
+constexpr bool row_fits(int64_t nx, size_t elem) { return nx * (int64_t)elem <= 0xffffffffLL; }
 
 // Tiles: R rows per wave, NW waves (launch_shape in k3s.hip chooses): the
 // larger and the smaller one of Alg 1 and the delta form, and that of the

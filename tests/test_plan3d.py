@@ -1,6 +1,7 @@
 """The cut of the 3D sweep passes into workgroups (csrc/plan3d.h, host code):
 every workgroup of a tolerance pass has a row of the partial sums that
-mx_workspace_size counts, over wide, thin and ordinary boxes."""
+mx_workspace_size counts, over wide, thin and ordinary boxes; rows whose byte
+offsets need more than 32 bits are refused."""
 import os
 import shutil
 import subprocess
@@ -25,7 +26,7 @@ int main() {
                 const Split p = split(s, k, nx, ny, nz, cus);
                 most = std::max(most, (long long)p.gx * p.gy * p.nzc);
             }
-        std::printf("%lld\n", most);
+        std::printf("%lld %d\n", most, row_fits(nx, f64 ? 8 : 4));
     }
 }
 """
@@ -58,7 +59,19 @@ def test_every_workgroup_has_a_row_of_partial_sums(driver):
     sizes += [(nx, 1, 1) for nx in range(900, 2200, 7)] + [(1000000, 3, 1), (256, 256, 256), (160, 144, 128)]
     cases = [(dtype, n, cus) for dtype in ("f32", "f64") for n in sizes for cus in (1, 256, 4096)]
     text = "".join(f"{int(d == 'f64')} {n[0]} {n[1]} {n[2]} {c}\n" for d, n, c in cases)
-    out = subprocess.run([driver], input=text, capture_output=True, text=True, check=True).stdout.split()
+    out = subprocess.run([driver], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
     assert len(out) == len(cases)
-    for (dtype, n, cus), wg in zip(cases, out):
-        assert int(wg) <= _rows(dtype, n), (dtype, n, cus, wg)
+    for (dtype, n, cus), line in zip(cases, out):
+        assert int(line.split()[0]) <= _rows(dtype, n), (dtype, n, cus, line)
+
+
+def test_rows_of_4_gib_are_refused(driver):
+    """The kernels keep a row's length in 32 bits of bytes: every width that
+    mx_validate accepts is either swept with that length or refused."""
+    cases = [(dtype, nx) for dtype in ("f32", "f64") for nx in (1, 4096, 2 ** 28, 2 ** 29 - 1, 2 ** 29, 2 ** 29 + 1, 2 ** 30)]
+    text = "".join(f"{int(d == 'f64')} {nx} 1 1 256\n" for d, nx in cases)
+    out = subprocess.run([driver], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    for (dtype, nx), line in zip(cases, out):
+        assert mx.validate(mx.make_config(3, (nx, 1, 1), 0.3, (1.0, 1.0, 1.0), dtype, mx.MX_ALL, 3)) == 0
+        row = nx * (8 if dtype == "f64" else 4)
+        assert (line.split()[1] == "1") == (row % 2 ** 32 == row), (dtype, nx)
