@@ -20,6 +20,7 @@
 // so the 4 x 4 node window starting one node before the start cell covers
 // both shapes.
 #include <algorithm>
+#include <limits>
 
 #include "mx_internal.h"
 
@@ -53,7 +54,8 @@ __device__ __forceinline__ int wrapc(int i, int n)
 // remainder steps (Markstein: with r correctly rounded and the estimate
 // within an ulp, the second is the correctly rounded quotient; the product
 // x r alone can be 1.5 ulp off).  Five operations against the ten or so of a
-// division, wherever one divisor serves several quotients.
+// division, wherever one divisor serves several quotients.  d is finite (the
+// remainder of an infinite one would be NaN); r = 0 gives x / infinity = 0.
 template <typename T>
 __device__ __forceinline__ T divr(T x, T d, T r)
 {
@@ -146,6 +148,9 @@ __global__ __launch_bounds__(PT) void k_pic_push(PicArgs<T> a, const FPair<T> *e
     const int64_t p0 = (int64_t)blockIdx.x * PT * ppt;   // the workgroup's first particle (exists)
     const int nx = a.nx, ny = a.ny, tid = threadIdx.x;
     const T dx = a.dx, dy = a.dy, dt = a.dt, rdx = T(1) / dx, rdy = T(1) / dy;
+    // gamma overflows from |u| of 1.8e19 (FP64 1.3e154): the particle's velocity
+    // rounds to zero
+    constexpr T huge = std::numeric_limits<T>::max();
     // cells relative to the first particle's, by the shorter way around the
     // periodic box: a window may cross its edge
     const int iref = (int)floor(divr(a.x[p0], dx, rdx)), jref = (int)floor(divr(a.y[p0], dy, rdy));
@@ -257,8 +262,8 @@ __global__ __launch_bounds__(PT) void k_pic_push(PicArgs<T> a, const FPair<T> *e
         const T h = a.h;
         const T umx = uf[0] + h * ex, umy = uf[1] + h * ey, umz = uf[2] + h * ez;
         const T gm = sqrt(T(1) + umx * umx + umy * umy + umz * umz);
-        const T rgm = T(1) / gm;
-        const T tx = divr(h * bx, gm, rgm), ty = divr(h * by, gm, rgm), tz = divr(h * bz, gm, rgm);
+        const T rgm = T(1) / gm, gmf = fmin(gm, huge);
+        const T tx = divr(h * bx, gmf, rgm), ty = divr(h * by, gmf, rgm), tz = divr(h * bz, gmf, rgm);
         const T upx = umx + (umy * tz - umz * ty);
         const T upy = umy + (umz * tx - umx * tz);
         const T upz = umz + (umx * ty - umy * tx);
@@ -269,9 +274,9 @@ __global__ __launch_bounds__(PT) void k_pic_push(PicArgs<T> a, const FPair<T> *e
         const T uplz = umz + (upx * sy - upy * sx);
         const T nux = uplx + h * ex, nuy = uply + h * ey, nuz = uplz + h * ez;
         const T g = sqrt(T(1) + nux * nux + nuy * nuy + nuz * nuz);
-        const T rg = T(1) / g;
-        const T x1 = x0 + divr(dt * nux, g, rg), y1 = y0 + divr(dt * nuy, g, rg);
-        const T vz = divr(nuz, g, rg);
+        const T rg = T(1) / g, gf = fmin(g, huge);
+        const T x1 = x0 + divr(dt * nux, gf, rg), y1 = y0 + divr(dt * nuy, gf, rg);
+        const T vz = divr(nuz, gf, rg);
         // Esirkepov: shapes of the start and end positions on the window of
         // nodes ic - 1 .. ic + 2, jc - 1 .. jc + 2 (the start position's
         // outer weights are zero)
