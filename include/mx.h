@@ -114,7 +114,8 @@ typedef struct mx_config {
                              most allowed). */
     int variant;          /* 2D sweep kernel: 0 library choice (with
                              sweeps_per_pass = 0, on grids of up to 1.3 to 5.5
-                             million cells by dtype, blocks and solve: register
+                             million cells by dtype, blocks and solve (fewer
+                             where a side is shorter than 256): register
                              tiles, which cut a fixed count into passes by a
                              time model of their own and a tolerance solve at
                              the depths below; else FP32: 4, FP64 and the

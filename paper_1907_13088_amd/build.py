@@ -45,7 +45,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     """Compile every source for gfx950 and link libmx.so (always rebuilds
     when force is set)."""
     srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
-    deps = [os.path.join(CSRC, s) for s in srcs] + [os.path.join(CSRC, h) for h in ("mx_internal.h", "k2s_impl.h", "k2f_impl.h", "k2fs_impl.h", "kbatch_impl.h", "stencil2d.h", "k2tile.h", "k2small_impl.h", "k2r_impl.h", "plan3d.h", "gridbar.h")] + [
+    deps = [os.path.join(CSRC, s) for s in srcs] + [os.path.join(CSRC, h) for h in ("mx_internal.h", "k2s_impl.h", "k2f_impl.h", "k2fs_impl.h", "kbatch_impl.h", "stencil2d.h", "k2tile.h", "k2small_impl.h", "k2r_impl.h", "plan2r.h", "plan3d.h", "gridbar.h")] + [
                                                     os.path.join(HERE, "..", "include", "mx.h")]
     if not force and os.path.exists(OUT) and all(os.path.getmtime(OUT) >= os.path.getmtime(d) for d in deps):
         return OUT

@@ -612,8 +612,8 @@ hipError_t launch_geo(const Coef<T> &c, int mask, int kind, const RegArgs<T> &a,
     return hipErrorInvalidValue;
 }
 
-// one pass over the blocks of `mask` on the
-// geometry `geo` (index into GEO of k2r.hip); *npart receives the workgroups per block
+// one pass over the blocks of `mask` on the geometry `geo` (index into GEO of
+// plan2r.h); *npart receives the workgroups per block
 template <typename T, int FORM, bool TOL>
 hipError_t launch(const Coef<T> &c, int mask, int geo, int kind, const RegArgs<T> &a, hipStream_t s, int *npart)
 {

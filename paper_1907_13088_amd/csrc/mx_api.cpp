@@ -165,9 +165,13 @@ struct mx_grid {
     int variant;          // 2D sweep kernel in use: 1 LDS tile, 2 row streaming (blocks
                           // together), 3 row streaming (each block on its own), 4 as 2
                           // with the front fused into the first pass where possible
-    bool reg = false;     // 2D, library choice: fixed counts run on register tiles
+    bool reg = false;     // 2D, library choice: fixed counts may run on register tiles
     RegPlan plan[2][3];   // their plans ([front][block set - 1]) for the counts plan_m
     int plan_m[2][3] = {{-1, -1, -1}, {-1, -1, -1}};
+    struct {
+        int m = -1, steps = 0, filter = 0;
+        bool ok = false;
+    } reg_last[2];            // the last answer of reg_ok, [front]
     RegPlan tol_plan{-1, 0, 0.0};  // register tiles of a tolerance solve (geo < 0: not used)
     int tol_stride = 0;       // norms per block and launch the workspace holds
     int tol_passes = 1, tol_ahead = 1;   // tested passes per step, steps queued ahead of the host
@@ -324,16 +328,16 @@ static void grid_setup(mx_grid *g, const mx_config *cfg, hipStream_t stream, int
         if (stream_workgroups(cfg, g->variant, cu) < cu / 2) g->variant = 1;
     }
     pass_depths(cfg, g->variant, g->spp);
-    // grids of up to a few million cells: register tiles
+    // register tiles, where plan2r.h has them faster
     const bool f64 = cfg->dtype == MX_F64, cheb = cfg->solver == MX_SOLVER_CHEBYSHEV;
-    const bool lib = cfg->ndim == 2 && cfg->variant == 0 && cfg->sweeps_per_pass == 0;
-    g->reg = lib && reg_pays(f64, cfg->blocks, false, cheb, cfg->n[0], cfg->n[1]);
-    if (lib && cfg->tol > 0.0 && !cfg->lumped && cfg->sweeps > 0 &&
-        reg_pays(f64, cfg->blocks, true, cheb, cfg->n[0], cfg->n[1])) {
+    g->reg = cfg->ndim == 2 && cfg->variant == 0 && cfg->sweeps_per_pass == 0;
+    if (g->reg && cfg->tol > 0.0 && !cfg->lumped && cfg->sweeps > 0) {
         // norms: three values per block and workgroup in the partial-sum buffer
+        const int k = g->spp[(cfg->blocks & 1) ? 0 : 1];
         g->tol_stride = (int)std::min<int64_t>(max_wg(cfg) / 3, 0x7fffffff);
-        g->tol_plan = reg_tol_plan(f64, cfg->blocks, cheb, cfg->n[0], cfg->n[1], g->spp[(cfg->blocks & 1) ? 0 : 1],
-                                   g->tol_stride);
+        g->tol_plan = reg_tol_plan(f64, cfg->blocks, cheb, cfg->n[0], cfg->n[1], k, g->tol_stride);
+        if (!reg_tol_pays(g->tol_plan, f64, cfg->blocks, cheb, cfg->form == MX_FORM_DELTA, cfg->n[0], cfg->n[1], k))
+            g->tol_plan.geo = -1;
     }
     const size_t arr = up((size_t)g->ncell * elem_of(cfg));
     char *p = g->ws;
@@ -791,6 +795,30 @@ const RegPlan &reg_plan_of(mx_grid *g, int blocks, bool front, int m)
     return p;
 }
 
+// Whether nsteps fixed-count steps (`front`) or solves run on register tiles:
+// by their sweeps, or the mean of the replayed counts (two per step)
+bool reg_ok(mx_grid *g, bool front, int nsteps, const int *replay)
+{
+    const mx_config &c = g->cfg;
+    if (!g->reg) return false;
+    long long sum = 0;
+    for (int s = 0; replay && s < nsteps; s++) {
+        int m = 0;
+        for (int b = 0; b < 2; b++)
+            if (c.blocks & (1 << b)) m = std::max(m, replay[2 * s + b]);
+        sum += m;
+    }
+    const int m = replay ? (int)((sum + nsteps / 2) / nsteps) : (c.lumped ? 0 : c.sweeps);
+    const bool filter = front && g->has_j && c.filter_passes > 0;
+    auto &last = g->reg_last[front];   // (a run repeats its calls)
+    if (last.m != m || last.steps != nsteps || last.filter != filter) {
+        last.ok = reg_pays(reg_plan_of(g, c.blocks, front, m), c.dtype == MX_F64, c.blocks,
+                           c.solver == MX_SOLVER_CHEBYSHEV, front, c.n[0], c.n[1], m, nsteps, filter);
+        last.m = m, last.steps = nsteps, last.filter = filter;
+    }
+    return last.ok;
+}
+
 // Buffers of the pass that reads iterate buffer cb (-1: the right-hand side
 // itself) and writes ob; the Chebyshev increments ping-pong with the iterate
 // (S, D2), the delta form's running sum stays in S
@@ -1158,7 +1186,7 @@ int run_sweeps(mx_grid *g, void *const rhs[3], const int *target_in, bool tolmod
 {
     e_done[0] = e_done[1] = false;
     if (tolmode) return solve_tol<T>(g, rhs, target_in, res, st);
-    if (g->reg && !E_fuse) {
+    if (!E_fuse && reg_ok(g, false, 1, target_in)) {
         int t[2];
         for (int b = 0; b < 2; b++) t[b] = (g->cfg.blocks & (1 << b)) ? target_in[b] : 0;
         return reg_solve<T>(g, nullptr, rhs, t, res);   // the transposed step's solve (no record asked for)
@@ -1346,10 +1374,7 @@ int step_impl(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
         const int rc = small_steps<T>(g, nsteps, env, stats);
         if (rc) return rc;
         nsteps = 0;   // done; the hand-back below returns B to the caller's buffers
-    } else if (g->reg && !tolmode &&
-               (nsteps >= 8 || g->ncell <= REG_FEW || !g->has_j || c.filter_passes == 0)) {
-        // (the filter runs apart here, once per call: on the larger grids it
-        // would cost short calls what the tiles gain, 30 us at 2048^2 FP64)
+    } else if (!tolmode && nsteps > 0 && reg_ok(g, true, nsteps, replay)) {
         const int rc = reg_steps<T>(g, nsteps, env, replay, stats);
         if (rc) return rc;
         nsteps = 0;

@@ -7,6 +7,7 @@
 #include <atomic>
 
 #include "../../include/mx.h"
+#include "plan2r.h"
 
 namespace mx {
 
@@ -288,8 +289,8 @@ struct SmallStat {
     int nonfinite;        // bit 0: ||dE'||, bit 1: a residual
     int finished;         // every block converged or at its count (register tiles)
 };
-// Register-tile passes for grids too small for row streams (k2r_impl.h)
-enum : int { RK_FRONT = 0, RK_MID = 1, RK_LAST = 2 };   // kinds of pass
+// Register-tile passes for grids too small for row streams (k2r_impl.h,
+// plan2r.h)
 // Tolerance solve: a block's state between the launches of a step
 struct RegTolBlock {
     double rhsn, resid;   // ||dE'||, ||x_(j+1) - x_j|| of the last tested pass
@@ -343,34 +344,13 @@ struct RegArgs {
     T cheb[2][2][16];     // Chebyshev form: per block and sweep of the pass, the factors
     RegTol tol;
 };
-// How one solve of m sweeps of a block set is cut: the tile geometry and the
-// number of passes (front + others when `front`, else passes without one)
-struct RegPlan {
-    int geo, passes;
-    double us;            // modelled time
-};
-RegPlan reg_plan(bool f64, int blocks, bool cheb, bool front, int64_t nx, int64_t ny, int m);
-// geometry of a tolerance solve whose tested passes have k sweeps, in
-// launches of nearly equal depth, with at most `stride` workgroups per block
-// (geo < 0: none); passes: launches of a tested pass
-RegPlan reg_tol_plan(bool f64, int blocks, bool cheb, int64_t nx, int64_t ny, int k, int64_t stride);
-// grids that the register tiles step faster than the row streams do
-bool reg_pays(bool f64, int blocks, bool tol, bool cheb, int64_t nx, int64_t ny);
-constexpr int64_t REG_FEW = (int64_t)17 << 17;   // cells up to which they do in calls of a few steps too (the filter runs apart)
 template <typename T>
 hipError_t launch_reg(const Coef<T> &c, int blocks, int geo, int kind, int form, bool tol, const RegArgs<T> &a, hipStream_t s,
                       int *npart);
 template <typename T>
 hipError_t launch_reg_finish(const RegFinish<T> &f, hipStream_t s);
 // The same passes over the grids of a batch, both blocks, fixed counts
-// (k2r_batch.hip).  kf: sweeps of the front's pass; ks: of the deepest other
-struct RegBatchPlan {
-    int geo, passes, kf, ks;
-};
-// geo < 0: the row streams are faster
-RegBatchPlan reg_batch_plan(const mx_config *cfgs, int ng);
-// tiles of a grid in a pass of `kind` cut for `cut` sweeps
-int64_t reg_batch_tiles(int geo, int kind, int cut, int64_t nx, int64_t ny);
+// (k2r_batch.hip)
 struct RegBatchPass {
     int kind, k, cut;   // sweeps, and the sweeps its tiles are cut for
     int first;          // no sweeps before: the iterate is dE'
