@@ -115,7 +115,8 @@ typedef struct mx_config {
     int variant;          /* 2D sweep kernel: 0 library choice (with
                              sweeps_per_pass = 0, on grids of up to 1.3 to 5.5
                              million cells by dtype, blocks and solve (fewer
-                             where a side is shorter than 256): register
+                             in steps of fewer than 8 to 12 sweeps, and where
+                             a side is shorter than 256): register
                              tiles, which cut a fixed count into passes by a
                              time model of their own and a tolerance solve at
                              the depths below; else FP32: 4, FP64 and the
@@ -349,8 +350,9 @@ int mx_sources_project(mx_grid *g, int nsrc, int W, const int64_t *origins, cons
  * times candidate pass depths and chunk lengths on workspace scratch
  * fields (the bound state is never touched), separately for the grouped
  * and the persistent schedule, and keeps the fastest of each.  With
- * sweeps_per_pass = 0 the grouped schedule of a batch of up to 3.4 (FP32; 2.9
- * with fewer than 12 sweeps) or 7.3 (FP64) million cells runs on register
+ * sweeps_per_pass = 0 the grouped schedule of a batch of up to 3.4 (FP32; 2
+ * to 2.9 with fewer than 12 sweeps) or 7.3 (FP64; 1.3 to 1.8 with fewer than
+ * 5) million cells, unless its grids are thin, runs on register
  * tiles instead, as single grids do (variant 0); the results are the same
  * bitwise.  The chosen
  * plans are kept in a text file and reused by a later init of the same

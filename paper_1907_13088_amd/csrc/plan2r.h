@@ -184,20 +184,42 @@ inline RegPlan reg_tol_plan(bool f64, int blocks, bool cheb, int64_t nx, int64_t
 // million; TM alone (streamed 12 sweeps deep) 2048 x 1600 132 against 147,
 // 2048^2 164 against 158: 3.4 million.
 // Chebyshev, 7 sweeps: FP32 1500 x 1100 70 against 93, 2048 x 1600 129 against
-// 120; FP64 131 against 141, 244 against 241: 2.2 million.
-inline int64_t reg_cells(bool f64, int blocks, bool cheb)
+// 120: 2.2 million; FP64 both blocks 1024 x 1000 98 against 140, 1500 x 1100 131 against 141 in
+// long calls but 176 against 158 in calls of a step, 1500 x 1400 237 against 193 so: 1.6
+// million; one block 2 million.
+// A step of few sweeps leaves the tiles little to win (their fronts and launches
+// cost more than the streams' where the grid is large), so the limit falls with
+// the sweeps m.  3 sweeps, tiles against streams in % of the streams' time: FP32 both blocks
+// 1500 x 1100 93, 2048 x 1450 118; FP64 both 1500 x 1100 98, 2048^2 122, TE 2048^2 143; Chebyshev
+// FP64 1024 x 1000 102, 1500 x 1100 141.  6 sweeps: FP32 both 1500 x 1400 86, 2048 x 1600 111;
+// FP64 both 1500 x 1100 82, 1500 x 1400 108, TE 2048 x 1450 103, 2048 x 1600 135 (8: 94).
+// By m at -3, 0, 3, 6, 8 and 12 and more, linear between, in units of 2^16 cells
+// (of 700 drawn sizes, counts and calls the slower kernel is taken by more than 10 % on a dozen).
+constexpr double REG_M[6] = {-3, 0, 3, 6, 8, 12};
+constexpr int REG_CELLS[2][2][3][6] = {
+    {{{12, 25, 36, 52, 70, 84}, {12, 25, 40, 60, 84, 84}, {12, 14, 24, 40, 46, 52}},     // FP32 TE, TM, both
+     {{8, 17, 26, 42, 66, 66}, {10, 20, 28, 46, 52, 52}, {10, 14, 24, 30, 66, 66}}},     // FP64
+    {{{10, 10, 24, 32, 34, 34}, {10, 10, 24, 32, 34, 34}, {10, 10, 24, 32, 34, 34}},     // Chebyshev FP32
+     {{8, 10, 15, 30, 34, 34}, {8, 10, 15, 30, 34, 34}, {8, 8, 16, 22, 30, 30}}}};         // Chebyshev FP64
+inline int64_t reg_cells(bool f64, int blocks, bool cheb, double m)
 {
-    if (cheb) return (int64_t)17 << 17;
-    if (f64) return blocks != 2 ? (int64_t)33 << 17 : (int64_t)13 << 18;
-    return blocks != 3 ? (int64_t)21 << 18 : (int64_t)13 << 18;
+    const int *c = REG_CELLS[cheb][f64][blocks - 1];
+    int i = 0;
+    while (i < 4 && m > REG_M[i + 1]) i++;
+    const double w = std::min(1.0, std::max(0.0, (m - REG_M[i]) / (REG_M[i + 1] - REG_M[i])));
+    return (int64_t)((c[i] + w * (c[i + 1] - c[i])) * 65536.0);
 }
 
 constexpr int64_t REG_FEW = (int64_t)17 << 17;   // cells up to which calls of a few steps pay too
 
 // A call of `steps` steps of m sweeps each on the plan p (a transposed solve,
-// front = false: one step, no filter).  filter: the current is filtered in a
-// launch of its own, once per call: on the larger grids it would cost short
-// calls what the tiles gain, 30 us at 2048^2 FP64.
+// front = false, gains at every count: 3 sweeps, FP64, 2048^2 86 %).  filter: the
+// current is filtered in a launch of its own, once per call: a step of a short
+// call pays its share of it, worth about three sweeps (two of the Chebyshev
+// solve; 3 sweeps, FP32 both, 1024 x 1000: 55 us against 53 in calls of a step, 29 against 32
+// in calls of eight), and on the larger grids it would cost such calls what the
+// tiles gain, 30 us at 2048^2 FP64.  A step without sweeps (lumped; FP64 1299 x 617, 39 us
+// against 34) is told apart from one of a few.
 // Grids whose short side holds little of a tile, us per step of 20 sweeps, FP32, tiles
 // against streams: 46875 x 64 177 against 155, 187500 x 16 180 against 221, 375000 x 8
 // 302 against 311, 750000 x 4 549 against 511, 3000000 x 1 2095 against 1495; a million
@@ -208,7 +230,8 @@ inline bool reg_pays(const RegPlan &p, bool f64, int blocks, bool cheb, bool fro
                      bool filter)
 {
     using namespace reg2d;
-    const int64_t most = reg_cells(f64, blocks, cheb), n = side_of(most);
+    const double share = filter ? (cheb ? 2.0 : 3.0) / steps : 0.0;
+    const int64_t most = reg_cells(f64, blocks, cheb, !front ? 1e9 : m > 0 ? m - share : -2.0 - share), n = side_of(most);
     if (p.geo < 0 || nx * ny > most || (filter && steps < 8 && nx * ny > REG_FEW)) return false;
     if (std::min(nx, ny) >= SHORT) return true;
     return tiles_win(p.us, reg_plan(f64, blocks, cheb, front, n, n, m).us, 0.55, strip_cells(nx, ny, 240, 10), most);
@@ -251,7 +274,13 @@ inline bool reg_tol_pays(const RegPlan &p, bool f64, int blocks, bool cheb, bool
 // sweeps, 218 against 216.  FP64: 0.18 million, 12 sweeps, 30 against 123; 4.3
 // million, 20 sweeps, 367 against 485, 8 sweeps 250 against 255; 7.2 million
 // 587 against 770 and 395 against 413.
-inline int64_t reg_batch_cells(bool f64, int m) { return f64 ? (int64_t)14 << 19 : (int64_t)(m >= 12 ? 13 : 11) << 18; }
+// Fewer sweeps, in % of the streams' time: FP32 1 sweep 2.2 million 105, 3 sweeps 2.2 million 99,
+// 2.7 million 109; FP64 3 sweeps 1.7 million 90, 2.2 million 121, 7.2 million 125, 5 sweeps 93.
+inline int64_t reg_batch_cells(bool f64, int m)
+{
+    if (f64) return (int64_t)(m >= 5 ? 112 : m >= 3 ? 27 : 20) << 16;
+    return (int64_t)(m >= 12 ? 52 : m >= 5 ? 44 : m >= 3 ? 34 : 30) << 16;
+}
 
 inline int64_t reg_batch_tiles(int geo, int kind, int cut, int64_t nx, int64_t ny)
 {

@@ -102,3 +102,25 @@ def test_thin_grids(tiles):
     assert not any(got), [l for l, g in zip(no, got) if g]
     got = tiles(yes)
     assert all(got), [l for l, g in zip(yes, got) if not g]
+
+
+def test_few_sweeps_and_short_calls(tiles):
+    """A step of few sweeps, and one that pays the current's filter alone,
+    leaves the tiles little to win."""
+    no = [_fixed(0, 2048, 1450, m=3), _fixed(0, 2048, 1600, m=6), _fixed(1, 1500, 1400, m=3), _fixed(1, 2048, 2048, m=3),
+          _fixed(1, 1500, 1400, m=6), _fixed(1, 2048, 2048, m=3, blocks=1), _fixed(1, 2048, 1600, m=6, blocks=1),
+          _fixed(1, 1500, 1100, m=3, steps=1), _fixed(1, 1500, 1400, m=6, steps=1), _fixed(0, 1500, 1400, m=3, steps=1),
+          _fixed(0, 1500, 1400, m=3, steps=1, blocks=1), _fixed(1, 2048, 1450, m=0, filt=False),
+          _fixed(1, 1500, 1100, m=3, cheb=True), _fixed(1, 1024, 1000, m=3, steps=1, cheb=True),
+          _fixed(1, 1500, 1100, m=7, steps=1, cheb=True), _fixed(0, 1500, 1400, m=3, cheb=True),
+          _fixed(0, 1500, 1400, m=3, steps=1, cheb=True), _batch(0, 5, 900, 600, m=2), _batch(1, 8, 700, 400, m=3),
+          _batch(1, 8, 1000, 900, m=3)]
+    yes = [_fixed(0, 1500, 1100, m=8, steps=1), _fixed(0, 2048, 1600, m=20), _fixed(1, 2048, 2048, m=20),
+           _fixed(1, 2048, 1600, m=8), _fixed(0, 2048, 2048, m=20, blocks=1), _fixed(1, 1024, 1000, m=7, cheb=True),
+           _fixed(0, 1500, 1100, m=7, cheb=True), _fixed(0, 500, 400, m=3, steps=1), _fixed(1, 500, 400, m=3, steps=1),
+           _batch(0, 8, 500, 256, m=2), _batch(1, 8, 1000, 900, m=5), _batch(1, 8, 500, 256, m=3)]
+    yes += [("a", f, b, 0, 2048, 2048 if f else 1600, m, 0, 0) for f in (0, 1) for b in (1, 3) for m in (1, 3, 20)]
+    got = tiles(no)
+    assert not any(got), [l for l, g in zip(no, got) if g]
+    got = tiles(yes)
+    assert all(got), [l for l, g in zip(yes, got) if not g]
