@@ -238,14 +238,19 @@ inline bool reg_pays(const RegPlan &p, bool f64, int blocks, bool cheb, bool fro
 }
 
 // Tolerance solves: FP32 (two tested passes) 2048 x 1600 227 against 237,
-// 2048^2 286 against 286; FP64 (three) 379 against 436, 523 against 483: 3.4
-// million.  Chebyshev: FP64 (passes of four) 1024^2 301 against 356, 1500 x 1100
-// 453 against 429: 1.3 million.
+// 2048^2 286 against 286; delta form 2048 x 1450 92 %, 2048 x 1600 103 %: 3.4 million, both
+// blocks in delta form 3.1.  FP64: standard form (three) 2048 x 1600 379 against
+// 436, 2048^2 523 against 483, but with nine tested passes 2048 x 1450 774 against 748: 2.9
+// million both blocks, 3.4 one; delta form, whose passes read and write the
+// running sum too, both blocks 1500 x 1100 85 to 93 %, 1500 x 1400 104 to 114, 2048 x 1600
+// 117 to 132 (by the number of passes; three to twelve): 1.8 million, one block
+// 1800 x 1300 99, 2048 x 1450 104: 2.4 million.  Chebyshev: FP64 (passes of four) 1024^2
+// 301 against 356, 1500 x 1100 453 against 429: 1.3 million.
 inline int64_t reg_tol_cells(bool f64, int blocks, bool cheb, bool delta)
 {
-    (void)blocks, (void)delta;
     if (cheb) return f64 ? (int64_t)5 << 18 : (int64_t)17 << 17;
-    return (int64_t)13 << 18;
+    if (f64 && delta) return (int64_t)(blocks == 3 ? 7 : 9) << 18;
+    return (int64_t)(blocks != 3 ? 13 : f64 ? 11 : delta ? 12 : 13) << 18;
 }
 
 // A tolerance solve whose tested passes have k sweeps, on its plan.  Every

@@ -96,7 +96,7 @@ def test_thin_grids(tiles):
     no += [_batch(0, 8, 46875, 8), _batch(0, 8, 15625, 8)]
     yes = [_fixed(f, *n) for f in (0, 1) for n in ((1, 3000000), (16, 187500), (64, 46875), (187500, 16), (1, 60000),
                                                    (30000, 2), (15000, 4), (7500, 8))]
-    yes += [_tol(f, *n) for f in (0, 1) for n in ((64, 46875), (62500, 16), (64, 15625), (1, 60000), (3750, 16))]
+    yes += [_tol(f, *n) for f in (0, 1) for n in ((64, 40000), (62500, 16), (64, 15625), (1, 60000), (3750, 16))]
     yes += [_batch(f, 8, *n) for f in (0, 1) for n in ((1, 125000), (16, 7812), (7812, 16), (3125, 8), (1562, 16))]
     got = tiles(no)
     assert not any(got), [l for l, g in zip(no, got) if g]
@@ -120,6 +120,21 @@ def test_few_sweeps_and_short_calls(tiles):
            _fixed(0, 1500, 1100, m=7, cheb=True), _fixed(0, 500, 400, m=3, steps=1), _fixed(1, 500, 400, m=3, steps=1),
            _batch(0, 8, 500, 256, m=2), _batch(1, 8, 1000, 900, m=5), _batch(1, 8, 500, 256, m=3)]
     yes += [("a", f, b, 0, 2048, 2048 if f else 1600, m, 0, 0) for f in (0, 1) for b in (1, 3) for m in (1, 3, 20)]
+    got = tiles(no)
+    assert not any(got), [l for l, g in zip(no, got) if g]
+    got = tiles(yes)
+    assert all(got), [l for l, g in zip(yes, got) if not g]
+
+
+def test_delta_form_tolerance_solves(tiles):
+    """The delta form's passes move the running sum too: streamed from smaller
+    grids on, in FP64 above all."""
+    no = [_tol(1, *n, delta=True) for n in ((1500, 1400), (1800, 1300), (2048, 1450), (2048, 1600))]
+    no += [_tol(1, 2048, 1450, delta=True, blocks=b) for b in (1, 2)]
+    no += [_tol(0, 2048, 1600, delta=True), _tol(1, 2048, 1450)]
+    yes = [_tol(1, *n, delta=True) for n in ((700, 300), (1024, 1024), (1500, 1100))]
+    yes += [_tol(1, 1500, 1400, delta=True, blocks=b) for b in (1, 2)]
+    yes += [_tol(0, 2048, 1450, delta=True), _tol(0, 2048, 1600), _tol(1, 1800, 1300), _tol(1, 2048, 1600, blocks=1)]
     got = tiles(no)
     assert not any(got), [l for l, g in zip(no, got) if g]
     got = tiles(yes)
