@@ -174,7 +174,7 @@ struct mx_grid {
     } reg_last[2];            // the last answer of reg_ok, [front]
     RegPlan tol_plan{-1, 0, 0.0};  // register tiles of a tolerance solve (geo < 0: not used)
     int tol_stride = 0;       // norms per block and launch the workspace holds
-    int tol_passes = 1, tol_ahead = 1;   // tested passes per step, steps queued ahead of the host
+    int tol_passes = 0, tol_ahead = 1;   // tested passes per step (0: not known yet), steps queued ahead of the host
     Coef<float> cf;
     Coef<double> cd;
     // Chebyshev solve: per block, the factors (previous increment, residual)
@@ -1002,6 +1002,32 @@ int reg_steps(mx_grid *g, int nsteps, const double *env, const int *replay, mx_s
 // behind it do nothing and the host, which reads the records back once per
 // queue, goes on from there.  Sweep counts and iterates equal those of
 // testing after every pass on the host.
+// A pass too many costs a short launch, a stall a round trip to the host, so a
+// grid's first step is queued with the passes that its tolerance asks for, and
+// a stalled step goes on with those that its own norms ask for (128^2 FP64, four
+// passes: the first step of a grid 67 us, with one stall per pass 112; four
+// steps on the static scratch, a new grid at every call, 275 and 329).
+int tol_passes_guess(const mx_config &c, int spp)
+{
+    // Alg 1: A has its spectrum in [0, 2/3] (TE), and fields of physical
+    // wavelengths, most of them well inside, take about half the sweeps of its
+    // end; the Chebyshev solve gains sigma per sweep wherever they lie
+    const double rho = 2.0 / 3.0, s = std::sqrt(1.0 - rho), sigma = (1.0 - s) / (1.0 + s);
+    const double m = c.solver == MX_SOLVER_CHEBYSHEV ? std::log(c.tol / 2.0) / std::log(sigma) : 0.5 * std::log(c.tol) / std::log(rho);
+    return (int)std::min(std::max(1.0, std::ceil(m / spp)), std::ceil((double)c.sweeps / spp));
+}
+// of a step that has run `n` passes without meeting the tolerance
+int tol_passes_more(const mx_config &c, const SmallStat &r, int spp, int n)
+{
+    double need = 0.0;
+    for (int b = 0; b < 2; b++) {
+        const double q = r.resid[b] / r.rhsn[b];   // gained in done[b] sweeps
+        if (!(c.blocks & (1 << b)) || r.conv[b] || !(q > 0.0 && q < 1.0)) continue;
+        need = std::max(need, r.done[b] * std::log(c.tol) / std::log(q) / spp);
+    }
+    return std::max(n + 1, (int)std::ceil(std::min(need, 2.0 * n)));
+}
+
 template <typename T>
 int reg_tol_steps(mx_grid *g, int nsteps, const double *env, mx_step_stats *stats)
 {
@@ -1106,6 +1132,7 @@ int reg_tol_steps(mx_grid *g, int nsteps, const double *env, mx_step_stats *stat
         ch.front = ch.test = 0;
         return MX_OK;
     };
+    if (g->tol_passes == 0) g->tol_passes = tol_passes_guess(c, spp);
     int s = 0;
     bool resume = false;   // the step s has its front and some passes behind it
     Chain resume_ch;
@@ -1119,7 +1146,7 @@ int reg_tol_steps(mx_grid *g, int nsteps, const double *env, mx_step_stats *stat
             if (i == 0 && resume) {
                 ch = resume_ch;
                 for (int q = 0; q < 3; q++) locs[i][q] = bloc0[q];
-                rc = queue_pass(false);
+                while (rc == MX_OK && ch.swe < target && ch.swe < g->tol_passes * spp) rc = queue_pass(false);
             } else {
                 ch = Chain{};
                 base = RegArgs<T>{};
@@ -1167,8 +1194,7 @@ int reg_tol_steps(mx_grid *g, int nsteps, const double *env, mx_step_stats *stat
             resume_ch = chains[i];
             for (int q = 0; q < 3; q++) bloc0[q] = locs[i][q];
             t0.epoch++;
-            // one pass more than it had
-            g->tol_passes = std::max(g->tol_passes, (chains[i].swe + spp - 1) / spp + 1);
+            g->tol_passes = tol_passes_more(c, hs[i], spp, (chains[i].swe + spp - 1) / spp);
             g->tol_ahead = std::max(1, g->tol_ahead / 4);
         } else {
             g->tol_passes = most;
