@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "mx_internal.h"
+#include "plan3d.h"
 
 namespace mx {
 namespace {
@@ -359,13 +360,11 @@ hipError_t launch_front3d(const Coef<T> &c, int filter_passes, const FrontArgs<T
     using G = Geo<T>;
     const void *k = p == 0 ? (const void *)k3_front<T, 0> : p == 1 ? (const void *)k3_front<T, 1>
                                                                    : (const void *)k3_front<T, 2>;
-    // z chunks: every workgroup marches its chunk and the steps that fill the
-    // z filter and the B planes below it, in rounds of the resident
-    // workgroups; the count with the fewest plane steps is taken.  Chunks as
-    // short as two planes fill the CUs on small grids (48 x 40 x 32 FP64, whole
-    // step: 86 us against 126 with chunks of 16 planes or more), and a second
-    // round that holds a few workgroups is avoided (160 x 144 x 128 FP64: 216
-    // workgroups of 36 steps, 153 us, against 270 of 30 in two rounds, 225)
+    // Chunks as short as two planes fill the CUs on small grids (48 x 40 x 32
+    // FP64, whole step: 86 us against 126 with chunks of 16 planes or more), and
+    // a second round that holds a few workgroups is avoided (160 x 144 x 128
+    // FP64: 216 workgroups of 36 steps, 153 us, against 270 of 30 in two
+    // rounds, 225)
     static std::atomic<int> resident[3][MX_MAX_DEVICES];
     const int slots = per_device(resident[p], [k] {
         int o = 0, dev = 0, cu = 0;
@@ -375,14 +374,9 @@ hipError_t launch_front3d(const Coef<T> &c, int filter_passes, const FrontArgs<T
         return o * cu;
     });
     const int gx = (c.nx + G::FX - 1) / G::FX, gy = (c.ny + G::FY - 1) / G::FY;
-    int nzc = 1, Lz = c.nz;
-    double best = 1e300;
-    for (int n = 1; n <= std::max(1, c.nz / 2); n++) {
-        const int L = (c.nz + n - 1) / n, m = (c.nz + L - 1) / L;
-        const double steps = (double)(((int64_t)gx * gy * m + slots - 1) / slots) * (L + 2 + std::max(1, 2 * p - 2));
-        if (steps < best * (1.0 - 1e-9)) best = steps, nzc = m, Lz = L;
-    }
-    dim3 g(gx, gy, nzc);
+    const plan3d::Chunks z = plan3d::front_chunks((int64_t)gx * gy, c.nz, 2 + std::max(1, 2 * p - 2), slots);
+    const int Lz = z.Lz;
+    dim3 g(gx, gy, z.nzc);
     *nwg = g.x * g.y * g.z;
     if (p == 0) hipLaunchKernelGGL((k3_front<T, 0>), g, dim3(G::FT), 0, s, c, a, Bin[0], Bin[1], Bin[2], Lz);
     else if (p == 1) hipLaunchKernelGGL((k3_front<T, 1>), g, dim3(G::FT), 0, s, c, a, Bin[0], Bin[1], Bin[2], Lz);

@@ -46,10 +46,32 @@ inline Split split(Shape s, int k, int nx, int ny, int nz, int cus)
     const int ox = out_x(k), oy = out_y(s, k);
     Split best{(nx + ox - 1) / ox, (ny + oy - 1) / oy, nz, 1, 1e300};
     const int64_t ncol = (int64_t)best.gx * best.gy;
+    // (more chunks only add fills and drains once the CUs are shared evenly, so
+    // the search ends after some hundreds of steps however long the box is)
     for (int n = 1; n <= std::max(1, nz / 2); n++) {
         const int Lz = (nz + n - 1) / n, nzc = (nz + Lz - 1) / Lz;
+        if ((double)ncol * (nz + 3.0 * k * nzc) / cus * (s.nw * s.r + 8) >= best.cost) break;   // below any cost from here on
         const double cost = (double)((ncol * nzc + cus - 1) / cus) * (Lz + 3 * k) * (s.nw * s.r + 8);
         if (cost < best.cost * (1.0 - 1e-9)) best.cost = cost, best.Lz = Lz, best.nzc = nzc;
+    }
+    return best;
+}
+
+// z chunks of the 3D front (k3f.hip): every workgroup marches its chunk and
+// `fill` plane steps that fill the z filter and the B planes below it, in rounds
+// of the `slots` resident workgroups; the count with the fewest plane steps.
+struct Chunks {
+    int Lz, nzc;
+};
+inline Chunks front_chunks(int64_t ncol, int nz, int fill, int slots)
+{
+    Chunks best{nz, 1};
+    double least = 1e300;
+    for (int n = 1; n <= std::max(1, nz / 2); n++) {
+        const int L = (nz + n - 1) / n, m = (nz + L - 1) / L;
+        if ((double)ncol * (nz + (double)fill * m) / slots >= least) break;   // as above
+        const double steps = (double)((ncol * m + slots - 1) / slots) * (L + fill);
+        if (steps < least * (1.0 - 1e-9)) least = steps, best = Chunks{L, m};
     }
     return best;
 }
