@@ -46,25 +46,6 @@ namespace reg2d {
 
 using front2d::avg6;
 
-// value of another lane (zero where there is none, or in rows outside ROWS)
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, true));
-}
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ double dpp(double v)
-{
-    const long long u = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xf, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-template <typename T>
-__device__ __forceinline__ T from_left(T v) { return dpp<0x138>(v); }    // wave_shr:1, lane - 1
-template <typename T>
-__device__ __forceinline__ T from_right(T v) { return dpp<0x130>(v); }   // wave_shl:1, lane + 1
-
 // value of column c - 1 / c + 1 of a lane's row of CPL columns
 template <typename T, int CPL>
 __device__ __forceinline__ T left_of(const T (&v)[CPL], int c) { return c > 0 ? v[c > 0 ? c - 1 : 0] : from_left(v[CPL - 1]); }
@@ -244,12 +225,12 @@ struct Tile {
 // scans and row broadcasts by DPP, a fifth of the latency of lane shuffles
 __device__ __forceinline__ double wave_sum(double v)
 {
-    v += dpp<0x111>(v);          // row_shr:1
-    v += dpp<0x112>(v);          // row_shr:2
-    v += dpp<0x114>(v);          // row_shr:4
-    v += dpp<0x118>(v);          // row_shr:8: the last lane of a row holds the row's sum
-    v += dpp<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
-    v += dpp<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3: the last lane holds all
+    v += lane_dpp<0x111>(v);          // row_shr:1
+    v += lane_dpp<0x112>(v);          // row_shr:2
+    v += lane_dpp<0x114>(v);          // row_shr:4
+    v += lane_dpp<0x118>(v);          // row_shr:8: the last lane of a row holds the row's sum
+    v += lane_dpp<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
+    v += lane_dpp<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3: the last lane holds all
     const long long u = __builtin_bit_cast(long long, v);
     const unsigned lo = __builtin_amdgcn_readlane((int)u, 63), hi = __builtin_amdgcn_readlane((int)(u >> 32), 63);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
