@@ -23,7 +23,8 @@
 // wave's own registers; LDS carries only the first and last row of each
 // wave, in a buffer per level and parity.  The valid columns shrink by one
 // per level on each side; along y the level-0 plane is loaded with one row
-// more on each side.  So a tile writes (64 - 2K) x (TY - 2(K - 1)) columns.
+// more on each side.  So a tile writes (64 - 2K) x (TY - 2(K - 1)) columns, a
+// wide one two more.
 // The carried value (dE' in the standard form, the running sum in the delta
 // form, dE' and the increment in the Chebyshev form) is read when level 1
 // completes a plane and then travels with the planes.
@@ -36,10 +37,14 @@
 // point from LDS, which measured, per pass: 512^3 FP32 delta form 2.11 ms
 // against 1.93 now, FP32 Alg 1 1.69 against 1.40 (ten sweeps, front taken
 // off), 256^3 FP64 0.38 against 0.32, Chebyshev FP64 at 250^3 8.64 ms per
-// step against 7.19.  The tile is 58 instead of 60 columns wide in FP32 with
-// three sweeps (60 instead of 62 in FP64 with two): where the grid's width is a
-// multiple of the wider tile only, the pass gains little or loses (180^3
-// FP32 Chebyshev: 1.12 ms per step against 1.19).
+// step against 7.19.
+// The first level has no neighbour for its outer lanes, which costs a tile two
+// columns (58 instead of 60 in FP32 with three sweeps, 60 instead of 62 in FP64
+// with two).  Where they add a column of tiles the wide tiles take those
+// neighbours from memory: one load per plane and wave, spread to the two lanes
+// by scalar reads, some 5 % of the pass (60 x 300 x 300 FP32, three sweeps, us per step:
+// delta form 1871 narrow, 1274 wide, 1264 by the kernel that read every point from LDS;
+// 62 x 300 x 300 FP64 6503, 4685, 4852; 180^3 FP32 delta 1424, 1326, 1331).
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -108,33 +113,53 @@ struct Row {
     T dx, dz, lxx;   // Dx' X (backward), Dx Z (forward), Dxx Z
 };
 
+// values of a row beyond the wave's first and last column
 template <typename T>
-__device__ __forceinline__ Row<T> row_of(const P3<T> &v)
+struct Edge {
+    P3<T> l, r;
+};
+// shifts with (W) and without such values
+template <bool W, typename T>
+__device__ __forceinline__ T left_of(T v, T edge)
 {
-    const T zr = from_right(v.z);
-    return Row<T>{v, v.x - from_left(v.x), zr - v.z, d2(from_left(v.z), v.z, zr)};
+    if constexpr (W) return from_left(v, edge);
+    else return from_left(v);
+}
+template <bool W, typename T>
+__device__ __forceinline__ T right_of(T v, T edge)
+{
+    if constexpr (W) return from_right(v, edge);
+    else return from_right(v);
 }
 
-// the quantities of the middle one of three rows
-template <typename T>
-__device__ __forceinline__ Q<T> inplane(const Row<T> &m, const Row<T> &c, const Row<T> &p)
+template <bool W, typename T>
+__device__ __forceinline__ Row<T> row_of(const P3<T> &v, const Edge<T> &e)
+{
+    const T zr = right_of<W>(v.z, e.r.z);
+    return Row<T>{v, v.x - left_of<W>(v.x, e.l.x), zr - v.z, d2(left_of<W>(v.z, e.l.z), v.z, zr)};
+}
+
+// the quantities of the middle one of three rows (em, ec, ep: their edges)
+template <bool W, typename T>
+__device__ __forceinline__ Q<T> inplane(const Row<T> &m, const Row<T> &c, const Row<T> &p, const Edge<T> &em, const Edge<T> &ec,
+                                        const Edge<T> &ep)
 {
     Q<T> q;
     q.X = c.v.x;
     q.Y = c.v.y;
     q.Z = c.v.z;
-    const T dy = c.v.y - m.v.y, dyz = p.v.z - c.v.z, dyr = from_right(dy);
+    const T dy = c.v.y - m.v.y, dyz = p.v.z - c.v.z, dyr = right_of<W>(dy, ec.r.y - em.r.y);
     q.lyyx = d2(m.v.x, c.v.x, p.v.x);
     q.pxy = dyr - dy;
     q.rxz = avg6(m.dz, c.dz, p.dz);
-    q.lxxy = d2(from_left(c.v.y), c.v.y, from_right(c.v.y));
+    q.lxxy = d2(left_of<W>(c.v.y, ec.l.y), c.v.y, right_of<W>(c.v.y, ec.r.y));
     q.pyx = p.dx - c.dx;
-    q.ryz = avg6(from_left(dyz), dyz, from_right(dyz));
+    q.ryz = avg6(left_of<W>(dyz, ep.l.z - ec.l.z), dyz, right_of<W>(dyz, ep.r.z - ec.r.z));
     q.lxxz = c.lxx;
     q.lyyz = d2(m.v.z, c.v.z, p.v.z);
     q.lxyz = d2(m.lxx, c.lxx, p.lxx);
     q.szx = avg6(m.dx, c.dx, p.dx);
-    q.szy = avg6(from_left(dy), dy, dyr);
+    q.szy = avg6(left_of<W>(dy, ec.l.y - em.l.y), dy, dyr);
     return q;
 }
 
@@ -163,7 +188,9 @@ __device__ __forceinline__ void setc(P3<T> &p, int q, T v)
 
 // FORM: FM_STD (x_l = b + A x_(l-1)), FM_DELTA (d_l = A d_(l-1), s_l = s_(l-1)
 // + d_l) or FM_CHEB (r = b + A x - x, d_l = f_l d_(l-1) + g_l r, x_l = x + d_l).
-template <typename T, int K, int FORM, bool LAST, int R, int NW>
+// WIDE: the first level takes the columns beyond a wave's own from memory, so
+// the valid columns shrink from the second level on.
+template <typename T, int K, int FORM, bool LAST, int R, int NW, bool WIDE>
 __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepArgs<T> a, int flags, int Lz)
 {
     constexpr bool DELTA = FORM == FM_DELTA, CHEB = FORM == FM_CHEB;
@@ -181,7 +208,8 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
     const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const int tl = xcd_map(lin, nwg);
     const int gxy = gridDim.x * gridDim.y;
-    constexpr int OX = 64 - 2 * K, OY = TY - 2 * (K - 1);   // output columns of a tile
+    constexpr int HX = WIDE ? K - 1 : K;   // columns a pass loses on each side
+    constexpr int OX = 64 - 2 * HX, OY = TY - 2 * (K - 1);   // output columns of a tile
     const int X0 = (tl % gridDim.x) * OX, Y0 = ((tl % gxy) / gridDim.x) * OY;
     const int Z0 = (tl / gxy) * Lz, Z1 = min(nz, Z0 + Lz);
     const size_t plane = (size_t)nx * ny;
@@ -190,11 +218,11 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
     // lane's offset along x serves all of them.  An offset past the row's
     // end drops a store, without a branch: every step issues the same
     // memory operations, and the wait for a load leaves later stores alone.
-    const int ux = X0 - K + lane, uy0 = Y0 - (K - 1) + w * R;
+    const int ux = X0 - HX + lane, uy0 = Y0 - (K - 1) + w * R;
     constexpr unsigned DROP = BUF_DROP;
     const unsigned row_bytes = (unsigned)nx * (unsigned)sizeof(T);
     const unsigned xin_off = (unsigned)wrapm(ux, nx) * (unsigned)sizeof(T);
-    const unsigned xout_off = lane >= K && lane < 64 - K && ux < nx ? xin_off : DROP;
+    const unsigned xout_off = lane >= HX && lane < 64 - HX && ux < nx ? xin_off : DROP;
     size_t row[R];
     bool outy[R];
 #pragma unroll
@@ -216,6 +244,12 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
         din[q] = first ? a.rhs[q] : a.s_in[q];
     }
     const unsigned din_off = first ? DROP : xin_off;   // no increment yet: zero
+    // WIDE: the edges of rows uy0 - 1 .. uy0 + R of a level-0 plane, one value
+    // per lane (row, component, side), in one load
+    const int er = min(lane / 6, R + 1), eq = (lane % 6) >> 1;
+    const T *const ebase = (eq == 0 ? xin[0] : (eq == 1 ? xin[1] : xin[2])) + (size_t)wrapm(uy0 - 1 + er, ny) * nx +
+                           wrapm(lane & 1 ? X0 - HX + 64 : X0 - HX - 1, nx);
+    T en = T(0), ev = T(0);   // of the plane in flight, and of the newest one
     auto load3 = [&](const T *const (&f)[3], size_t o, unsigned at) {
         return P3<T>{buf_load(f[0] + o, row_bytes, at), buf_load(f[1] + o, row_bytes, at),
                      buf_load(f[2] + o, row_bytes, at)};
@@ -252,6 +286,7 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
 #pragma unroll
         for (int r = 0; r < R; r++) px[r] = load3(xin, zin + row[r], in ? xin_off : DROP);
         pr = load3(xin, zin + rrow, in ? ring_off : DROP);
+        if (WIDE) en = ebase[zin];
     };
     int zt = wrapm(tbeg, nz), ze = wrapm(tbeg + 1 - 2 * K, nz);   // planes t and t + 1 - 2K, wrapped
     auto step = [&](const int t, auto out_) {
@@ -269,13 +304,28 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
                                  pl[l - 1][prd][slot][2][lane]};
                 };
                 const P3<T> below = edge(EDGE * w + EDGE + 1);
-                Row<T> rm = row_of<T>(edge(EDGE * w)), rc = row_of<T>(val[l - 1][0]);
+                const P3<T> above = edge(EDGE * w);
+                // edges of the row in slot i (0: the row above the wave's first)
+                auto side = [&](int i) {
+                    Edge<T> e{};
+                    if (WIDE && l == 1) {
+                        e.l = P3<T>{lane_read(ev, 6 * i), lane_read(ev, 6 * i + 2), lane_read(ev, 6 * i + 4)};
+                        e.r = P3<T>{lane_read(ev, 6 * i + 1), lane_read(ev, 6 * i + 3), lane_read(ev, 6 * i + 5)};
+                    }
+                    return e;
+                };
+                auto row_at = [&](const P3<T> &v, const Edge<T> &e) { return WIDE && l == 1 ? row_of<true>(v, e) : row_of<false>(v, e); };
+                Edge<T> em = side(0), ec = side(1);
+                Row<T> rm = row_at(above, em), rc = row_at(val[l - 1][0], ec);
 #pragma unroll
                 for (int r = 0; r < R; r++) {
-                    const Row<T> rp = row_of<T>(r + 1 < R ? val[l - 1][r + 1 < R ? r + 1 : r] : below);
-                    const Q<T> q = inplane<T>(rm, rc, rp);
+                    const Edge<T> ep = side(r + 2);
+                    const Row<T> rp = row_at(r + 1 < R ? val[l - 1][r + 1 < R ? r + 1 : r] : below, ep);
+                    const Q<T> q = WIDE && l == 1 ? inplane<true>(rm, rc, rp, em, ec, ep) : inplane<false>(rm, rc, rp, em, ec, ep);
                     rm = rc;
                     rc = rp;
+                    em = ec;
+                    ec = ep;
                     P3<T> f0, f1, f2;
                     fold<T>(z, q, f0, f1, f2);
                     const P3<T> ax = p3add(sa[l][r], f2);   // (A x) at plane o
@@ -354,6 +404,7 @@ __global__ __launch_bounds__(64 * NW) void k3_stream(Coef<T> c, Zc<T> z, SweepAr
         }
 #pragma unroll
         for (int r = 0; r < R; r++) val[0][r] = px[r];
+        ev = en;
         publish(0, pw, EDGE * w + 1, px[0]);
         if (EDGE > 1) publish(0, pw, EDGE * w + 2, px[R - 1]);
         if (ring) publish(0, pw, rslot, pr);
@@ -426,16 +477,23 @@ inline int cu_count()
     });
 }
 
-template <typename T, int K, int FORM, bool LAST, int R, int NW>
-hipError_t launch_k(const Coef<T> &c, const plan3d::Split &p, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+template <typename T, int K, int FORM, bool LAST, int R, int NW, bool WIDE>
+hipError_t launch_w(const Coef<T> &c, const plan3d::Split &p, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
 {
-    static_assert(K <= plan3d::kmax(sizeof(T) == 8) && plan3d::out_x(K) == 64 - 2 * K);
+    static_assert(K <= plan3d::kmax(sizeof(T) == 8) && plan3d::out_x(K, WIDE) == 64 - 2 * (WIDE ? K - 1 : K));
     dim3 g(p.gx, p.gy, p.nzc);
     *nwg = g.x * g.y * g.z;
     // a workgroup leaves its partial sums in a row of its own
     if (*nwg > plan3d::partial_rows(sizeof(T) == 8, c.nx, c.ny, c.nz)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k3_stream<T, K, FORM, LAST, R, NW>), g, dim3(64 * NW), 0, s, c, zcoef(c), a, flags, p.Lz);
+    hipLaunchKernelGGL((k3_stream<T, K, FORM, LAST, R, NW, WIDE>), g, dim3(64 * NW), 0, s, c, zcoef(c), a, flags, p.Lz);
     return hipGetLastError();
+}
+
+template <typename T, int K, int FORM, bool LAST, int R, int NW>
+hipError_t launch_k(const Coef<T> &c, const plan3d::Split &p, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
+{
+    if (p.wide) return launch_w<T, K, FORM, LAST, R, NW, true>(c, p, flags, a, s, nwg);
+    return launch_w<T, K, FORM, LAST, R, NW, false>(c, p, flags, a, s, nwg);
 }
 
 // Tiles.  Alg 1 and the delta form: two rows per wave (three or four halve the

@@ -134,6 +134,38 @@ __device__ __forceinline__ T from_left(T v) { return lane_dpp<0x138>(v); }    //
 template <typename T>
 __device__ __forceinline__ T from_right(T v) { return lane_dpp<0x130>(v); }   // wave_shl:1, lane + 1
 
+// the same, `edge` in the lane that has no such neighbour
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp_or(float edge, float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge), __builtin_bit_cast(int, v),
+                                                                 CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_dpp_or(double edge, double v)
+{
+    const long long u = __builtin_bit_cast(long long, v), e = __builtin_bit_cast(long long, edge);
+    const int lo = __builtin_amdgcn_update_dpp((int)e, (int)u, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(e >> 32), (int)(u >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+template <typename T>
+__device__ __forceinline__ T from_left(T v, T edge) { return lane_dpp_or<0x138>(edge, v); }
+template <typename T>
+__device__ __forceinline__ T from_right(T v, T edge) { return lane_dpp_or<0x130>(edge, v); }
+
+// value of lane `l` (the same for the whole wave)
+__device__ __forceinline__ float lane_read(float v, int l)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+__device__ __forceinline__ double lane_read(double v, int l)
+{
+    const long long u = __builtin_bit_cast(long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)u, l), hi = __builtin_amdgcn_readlane((int)(u >> 32), l);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
 // One value of an array of `bytes` bytes, `at` bytes from its start.  From
 // BUF_DROP, as from any offset past the end, a load gives zero and a store is
 // dropped (bounds check of raw buffers), so lanes without work need no branch
