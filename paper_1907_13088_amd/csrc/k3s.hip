@@ -509,8 +509,13 @@ hipError_t launch_k(const Coef<T> &c, const plan3d::Split &p, int flags, const S
 template <typename T, int K, int FORM, bool LAST>
 hipError_t launch_shape(const Coef<T> &c, int flags, const SweepArgs<T> &a, hipStream_t s, int *nwg)
 {
-    constexpr bool F64 = sizeof(T) == 8;
-    if constexpr (FORM == FM_CHEB) {
+    constexpr bool F64 = sizeof(T) == 8, CHEB = FORM == FM_CHEB;
+    if (plan3d::takes_low(F64, CHEB, K, c.nx, c.ny, c.nz)) {
+        // several workgroups of the lowest tiles share a CU
+        constexpr plan3d::Shape S = plan3d::low(F64, CHEB);
+        return launch_k<T, K, FORM, LAST, S.r, S.nw>(c, plan3d::split(S, K, c.nx, c.ny, c.nz, 2 * cu_count()), flags, a, s, nwg);
+    }
+    if constexpr (CHEB) {
         constexpr plan3d::Shape S = plan3d::cheb(F64);
         return launch_k<T, K, FORM, LAST, S.r, S.nw>(c, plan3d::split(S, K, c.nx, c.ny, c.nz, cu_count()), flags, a, s, nwg);
     } else {

@@ -1244,7 +1244,7 @@ int run_sweeps(mx_grid *g, void *const rhs[3], const int *target_in, bool tolmod
                     rem = std::min(rem, target[b] - done[b]);
                 }
             if (!act) break;
-            const int spp = (act & 1) ? g->spp[0] : g->spp[1];
+            const int spp = c.ndim == 3 && plan3d::flat(c.n[2]) ? 1 : ((act & 1) ? g->spp[0] : g->spp[1]);
             const int kk = rem / ((rem + spp - 1) / spp);
             const bool first = (act & 1) ? done[0] == 0 : done[1] == 0;
             // E += x fused into this pass when every active block of the group ends here

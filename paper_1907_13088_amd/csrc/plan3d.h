@@ -16,15 +16,16 @@ constexpr int kmax(bool f64) { return f64 ? 2 : 3; }
 // (0xffffffff) stands for "no cell"
 constexpr bool row_fits(int64_t nx, size_t elem) { return nx * (int64_t)elem <= 0xffffffffLL; }
 
-// Tiles: R rows per wave, NW waves (launch_shape in k3s.hip chooses): the
-// larger and the smaller one of Alg 1 and the delta form, and that of the
-// Chebyshev form
+// Tiles: R rows per wave, NW waves: the larger and the smaller one of Alg 1 and
+// the delta form, that of the Chebyshev form, and the lowest ones for boxes of
+// few rows or planes
 struct Shape {
     int r, nw;
 };
 constexpr Shape large(bool f64) { return {2, f64 ? 8 : 12}; }
 constexpr Shape small(bool f64) { return {2, f64 ? 4 : 8}; }
 constexpr Shape cheb(bool f64) { return {1, f64 ? 12 : 16}; }
+constexpr Shape low(bool f64, bool cheb) { return f64 && cheb ? Shape{1, 8} : Shape{2, 4}; }
 
 // A launch's z chunks and its time in the model that sizes it: a workgroup
 // marches Lz + 3K plane steps (its chunk and the pipeline's fill and drain),
@@ -89,17 +90,35 @@ inline Chunks front_chunks(int64_t ncol, int nz, int fill, int slots)
     return best;
 }
 
+// Boxes of one or two planes run passes of single sweeps: the pipeline's fill
+// and drain, three plane steps per sweep of the pass, are most of a march
+// (1024 x 1024 x 1, six Chebyshev sweeps, FP32 359 us per step in passes of three, 250 so).
+constexpr bool flat(int64_t nz) { return nz <= 2; }
+// The lowest tiles, for the passes of flat boxes and where the rows of a box fill
+// one of them, in wide boxes little more (a taller tile is mostly padding then;
+// us per step, FP32, lowest against taller tiles: 1024 x 1 x 1024 delta form 1093 against 2387, 65536 x 8
+// x 8 Alg 1 397 against 551, 200000 x 4 x 1 Chebyshev 335 against 691; 8 x 8 x 65536
+// Chebyshev 2320 against 2016).
+inline bool takes_low(bool f64, bool cheb, int k, int64_t nx, int64_t ny, int64_t nz)
+{
+    return (flat(nz) && k == 1) || ny <= (nx > 64 && !f64 ? 8 : out_y(low(f64, cheb), k));
+}
+
 // Rows of partial sums (one per workgroup) of any pass on this grid, whatever
 // the number of CUs: the tiles of the narrowest and lowest output, times the
 // most chunks.
 inline int64_t partial_rows(bool f64, int64_t nx, int64_t ny, int64_t nz)
 {
     int64_t rows = 0;
-    for (int k = 1; k <= kmax(f64); k++)
-        for (const Shape s : {large(f64), small(f64), cheb(f64)}) {
+    for (int k = 1; k <= kmax(f64); k++) {
+        auto count = [&](Shape s) {
             const int ox = out_x(k, false), oy = out_y(s, k);
             rows = std::max(rows, ((nx + ox - 1) / ox) * ((ny + oy - 1) / oy) * std::max<int64_t>(1, nz / 2));
-        }
+        };
+        count(large(f64)), count(small(f64)), count(cheb(f64));
+        for (const bool c : {false, true})
+            if (takes_low(f64, c, k, nx, ny, nz)) count(low(f64, c));
+    }
     return rows;
 }
 

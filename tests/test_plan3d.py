@@ -23,9 +23,12 @@ int main() {
     while (std::scanf("%d %d %d %d %d", &f64, &nx, &ny, &nz, &cus) == 5) {
         long long most = 0;
         for (int k = 1; k <= kmax(f64); k++)
-            for (const Shape s : {large(f64), small(f64), cheb(f64)}) {
-                const Split p = split(s, k, nx, ny, nz, cus);
-                most = std::max(most, (long long)p.gx * p.gy * p.nzc);
+            for (const bool c : {false, true}) {   // the tiles launch_shape may take
+                const bool lo = takes_low(f64, c, k, nx, ny, nz);
+                for (const Shape s : {lo ? low(f64, c) : c ? cheb(f64) : large(f64), lo ? low(f64, c) : c ? cheb(f64) : small(f64)}) {
+                    const Split p = split(s, k, nx, ny, nz, lo ? 2 * cus : cus);
+                    most = std::max(most, (long long)p.gx * p.gy * p.nzc);
+                }
             }
         std::printf("%lld %d\n", most, row_fits(nx, f64 ? 8 : 4));
     }
