@@ -352,9 +352,9 @@ int mx_sources_project(mx_grid *g, int nsrc, int W, const int64_t *origins, cons
  * and the persistent schedule, and keeps the fastest of each.  With
  * sweeps_per_pass = 0 the grouped schedule of a batch of up to 3.4 (FP32; 2
  * to 2.9 with fewer than 12 sweeps) or 7.3 (FP64; 1.3 to 1.8 with fewer than
- * 5) million cells, unless its grids are thin, runs on register
- * tiles instead, as single grids do (variant 0); the results are the same
- * bitwise.  The chosen
+ * 5) million cells, unless its grids are thin, runs on register tiles
+ * instead, as single grids do (variant 0), and is not timed; the results are
+ * the same bitwise.  The chosen
  * plans are kept in a text file and reused by a later init of the same
  * grid configs on the same device and library build: $MX_TUNE_CACHE (a
  * path; "0" or empty turns the cache off), else
@@ -369,9 +369,9 @@ int mx_batch_init(const mx_config *cfgs, int ngrids, void *stream, void *workspa
 int mx_batch_bind(mx_batch *b, int grid, void *const E[3], void *const B[3]);
 int mx_batch_step(mx_batch *b, int nsteps, int persistent);
 /* The row-streaming schedules: sweeps per pass of the grouped schedule (tuned
-   at init when the configs ask for sweeps_per_pass = 0; batches that run on
-   register tiles do not use it), its total work items of one step, and the
-   workgroups of the persistent launch. */
+   at init when the configs ask for sweeps_per_pass = 0; 5 for batches that run
+   on register tiles, which do not use it), its total work items of one step,
+   and the workgroups of the persistent launch. */
 int mx_batch_get_plan(mx_batch *b, int *sweeps_per_pass, int *tiles_total, int *persistent_blocks);
 /* One schedule's tuned shape (persistent = 0 grouped, 1 persistent): the
    deepest pass (sweeps), the rows of a sweep work item's chunk and of a

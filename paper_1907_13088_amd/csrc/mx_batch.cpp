@@ -545,7 +545,9 @@ int mx_batch_init(const mx_config *cfgs, int ngrids, void *stream, void *workspa
         const std::string path = tune_cache_path();
         const uint64_t key = tune_key(b);
         if (!tune_cache_load(b, path, key)) {
-            rc = b->dtype == MX_F64 ? autotune<double>(b, true, true) : autotune<float>(b, true, true);
+            // (a batch on register tiles steps the persistent schedule alone on row streams)
+            const bool grouped = b->reg.geo < 0;
+            rc = b->dtype == MX_F64 ? autotune<double>(b, grouped, true) : autotune<float>(b, grouped, true);
             if (rc) return rc;
             tune_cache_store(b, path, key);
         }
