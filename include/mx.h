@@ -91,7 +91,9 @@ extern "C" {
 
 typedef struct mx_config {
     int ndim;             /* 2 or 3 */
-    int64_t n[3];         /* cells per axis; n[2] ignored (1) in 2D */
+    int64_t n[3];         /* cells per axis; n[2] ignored (1) in 2D; 3D grids
+                             with rows of 4 GiB and more take no sweeps (mx_step
+                             and mx_adjoint refuse them) */
     double d[3];          /* cell sizes dx, dy, dz (> 0) */
     double dt;            /* time step, c = 1; must satisfy the CFL bound */
     int dtype;            /* MX_F32 or MX_F64 */
@@ -166,7 +168,10 @@ int mx_workspace_size(const mx_config *cfg, size_t *bytes);
 
 /* Create a grid.  `stream` is a hipStream_t (NULL = default stream);
    `workspace` a device buffer of at least mx_workspace_size() bytes, owned
-   by the caller and kept alive until mx_destroy.  Validates like
+   by the caller and kept alive until mx_destroy; it carries nothing from one
+   successful call to the next, but every call that launches work on the grid may write
+   it (mx_pic_push too), so grids that share one have to share the stream, and
+   nothing else may use it meanwhile.  Validates like
    mx_validate.  Sets the current device to the one `workspace` is on. */
 int mx_init(const mx_config *cfg, void *stream, void *workspace, size_t workspace_bytes,
             mx_grid **out);

@@ -36,8 +36,10 @@ struct Geo {
 inline constexpr Geo GEO[4] = {{64, 32}, {64, 32}, {64, 64}, {128, 64}};
 
 // Time of a pass (us) with c workgroups per CU: t0 + c load[kind] + k (c s + s0),
-// fitted to sweeps over grids from 128^2 to 2048^2, depths 0 to 14, every
-// geometry, each block alone and both in one launch (relative rms 5 to 20 %;
+// fitted to single passes over grids from 128^2 to 2048^2, every kind, depths 0, 2,
+// 4, 6, 8, 10 and 14, every geometry, each block alone and both in one launch:
+// per form, type, blocks and geometry one non-negative least-squares fit of the
+// six numbers to the measured times, each divided by its time (rms 5 to 20 %;
 // the choice it makes is within 3 % of the best measured one on average, 35 %
 // at worst).  By form (standard and delta, Chebyshev), type and blocks,
 // geometry.
@@ -305,6 +307,8 @@ inline RegBatchPlan reg_batch_plan(const mx_config *cfgs, int ng)
     if (cells > most) return best;
     double us = 1e29, meet = 1e29, strips = 0.0;
     const Fit *fit = FIT[0][f64 ? 5 : 2];
+    // (kb_reg is built for one column per lane: without the 128 x 64 region, which
+    // FP32 grids of some million cells prefer on their own)
     for (int g = 0; g < 3; g++) {
         const int kmax = std::min((GEO[g].ry - 4) / 2, 16);
         for (int n = std::max(2, (m + kmax - 1) / kmax); n <= m / 2 + 2; n++) {
