@@ -30,9 +30,9 @@
 // completes a plane and then travels with the planes.
 //
 // What bounds it: VALU issue and, with the 8 to 16 waves that fit a CU, the
-// latencies between two barriers (512^3, FP32, three sweeps: 61 % of the VALU
+// latencies between two barriers (512^3, FP32, three sweeps: 58 % of the VALU
 // cycles; the HBM traffic alone would take half the time).  Rows in registers
-// instead of planes in LDS take a quarter of the VALU and nine tenths of the
+// instead of planes in LDS take a quarter of the VALU and four fifths of the
 // LDS instructions away against a kernel that reads the 3 x 3 columns of each
 // point from LDS, which measured, per pass: 512^3 FP32 delta form 2.11 ms
 // against 1.93 now, FP32 Alg 1 1.69 against 1.40 (ten sweeps, front taken
